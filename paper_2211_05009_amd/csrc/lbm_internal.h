@@ -32,9 +32,9 @@ void tune_cache_store(const std::string &key, int variant);
 namespace lbm {
 struct SeriesDesc;
 }
-// Classify nseries series described on the host (d2q9_series.hpp), longest
-// n_max samples, on stream st; allocates its own device scratch.
-int classify_series_descs(const lbm::SeriesDesc *descs_host, int nseries, long long n_max,
+// Classify nseries series of n samples each described on the host
+// (d2q9_series.hpp) on stream st; allocates its own device scratch.
+int classify_series_descs(const lbm::SeriesDesc *descs_host, int nseries, long long n,
                           double steady_tol, double periodic_tol, int min_lag, int max_lag,
                           hipStream_t st, lbm_flow_state_t *out_host);
 

@@ -6,7 +6,6 @@
 #include <algorithm>
 #include <cmath>
 #include <mutex>
-#include <vector>
 
 #include "../../include/lbm.h"
 #include "d2q9_series.hpp"
@@ -14,52 +13,91 @@
 
 using namespace lbm;
 
-int classify_series_descs(const SeriesDesc *descs_host, int nseries, long long n_max,
+namespace {
+
+// Threads and chunk of k_series_lags' two forms.
+constexpr int kWideThreads = 256, kWideChunk = 960, kWideUnroll = 24;
+constexpr int kNarrowThreads = 64, kNarrowChunk = 512, kNarrowUnroll = 16;
+
+// Whether the lags take three lags per lane.  One lag per lane gives three
+// times the wavefronts but two LDS reads per sample and lag: it is faster
+// until its wavefronts fill the GPU's 1024 SIMDs about three deep.  Narrow
+// against wide, whole call: 1 x 10,000 samples (53 narrow wavefronts) 153 /
+// 341 us, 97 x 4000 (2037) 122 / 158, 153 x 3000 (2448) 106 / 119, 153 x
+// 10,000 (8109) 837 / 451.
+bool series_lags_wide(int nseries, long long nlags) {
+  return (long long)nseries * ((nlags + 63) / 64) > 3072;
+}
+
+// Issue the classification of nseries series of n samples from src on st:
+// work holds work_stride doubles per series, out nseries records (device).
+template <typename Src>
+hipError_t launch_classify(const Src &src, int nseries, long long n, double steady_tol,
+                           double periodic_tol, int min_lag, int max_lag, double *work,
+                           long long work_stride, lbm_flow_state_t *out, hipStream_t st) {
+  const long long nlags = series_max_lag(n, max_lag) - min_lag + 1;
+  hipLaunchKernelGGL(k_series_stats<Src>, dim3(nseries), dim3(kSeriesThreads), 0, st, src, n,
+                     steady_tol, work, work_stride);
+  if (series_lags_wide(nseries, nlags)) {
+    constexpr int W = 3 * kWideThreads;
+    hipLaunchKernelGGL((k_series_lags<3, kWideThreads, kWideChunk, kWideUnroll>),
+                       dim3((unsigned)(nseries * ((nlags + W - 1) / W))), dim3(kWideThreads), 0,
+                       st, work, work_stride, n, nseries, min_lag, nlags);
+  } else {
+    constexpr int W = kNarrowThreads;
+    hipLaunchKernelGGL((k_series_lags<1, kNarrowThreads, kNarrowChunk, kNarrowUnroll>),
+                       dim3((unsigned)(nseries * ((nlags + W - 1) / W))), dim3(kNarrowThreads),
+                       0, st, work, work_stride, n, nseries, min_lag, nlags);
+  }
+  hipLaunchKernelGGL(k_series_pick<lbm_flow_state_t>, dim3(nseries), dim3(kSeriesThreads), 0, st,
+                     work, work_stride, n, min_lag, nlags, periodic_tol, out);
+  return hipGetLastError();
+}
+
+// Classify into out_host with device scratch of this call: one allocation
+// holding the records, the descriptors (descs_host, may be null) and the
+// work memory.
+template <typename MakeSrc>
+int classify_alloc(const MakeSrc &make_src, const SeriesDesc *descs_host, int nseries,
+                   long long n, double steady_tol, double periodic_tol, int min_lag, int max_lag,
+                   hipStream_t st, lbm_flow_state_t *out_host) {
+  const long long stride = series_work_doubles(n);
+  const size_t out_bytes = (sizeof(lbm_flow_state_t) * nseries + 255) / 256 * 256;
+  const size_t desc_bytes = descs_host ? (sizeof(SeriesDesc) * nseries + 255) / 256 * 256 : 0;
+  char *mem = nullptr;
+  hipError_t e = hipMalloc(&mem, out_bytes + desc_bytes + sizeof(double) * stride * nseries);
+  if (e != hipSuccess)
+    return lbm_fail(e == hipErrorOutOfMemory ? LBM_ENOMEM : LBM_EDEVICE, "classify: %s",
+                    hipGetErrorString(e));
+  lbm_flow_state_t *d_out = reinterpret_cast<lbm_flow_state_t *>(mem);
+  SeriesDesc *d_desc = reinterpret_cast<SeriesDesc *>(mem + out_bytes);
+  double *d_work = reinterpret_cast<double *>(mem + out_bytes + desc_bytes);
+  if (descs_host)
+    e = hipMemcpyAsync(d_desc, descs_host, sizeof(SeriesDesc) * nseries, hipMemcpyHostToDevice,
+                       st);
+  if (e == hipSuccess)
+    e = launch_classify(make_src(d_desc), nseries, n, steady_tol, periodic_tol, min_lag, max_lag,
+                        d_work, stride, d_out, st);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(out_host, d_out, sizeof(lbm_flow_state_t) * nseries,
+                       hipMemcpyDeviceToHost, st);
+  const hipError_t es = hipStreamSynchronize(st);
+  if (e == hipSuccess) e = es;
+  (void)hipFree(mem);
+  if (e != hipSuccess)
+    return lbm_fail(e == hipErrorOutOfMemory ? LBM_ENOMEM : LBM_EDEVICE, "classify: %s",
+                    hipGetErrorString(e));
+  return LBM_OK;
+}
+
+}  // namespace
+
+int classify_series_descs(const SeriesDesc *descs_host, int nseries, long long n,
                           double steady_tol, double periodic_tol, int min_lag, int max_lag,
                           hipStream_t st, lbm_flow_state_t *out_host) {
   if (nseries <= 0) return LBM_OK;
-  // lags per series are at most n_max / 3 (or max_lag) -- room for n_max
-  const long long stride = 2 * n_max + 8;
-  SeriesDesc *d_desc = nullptr;
-  double *d_work = nullptr;
-  SeriesOut *d_out = nullptr;
-  int rc = LBM_OK;
-  hipError_t e = hipMalloc(&d_desc, sizeof(SeriesDesc) * nseries);
-  if (e == hipSuccess) e = hipMalloc(&d_work, sizeof(double) * stride * nseries);
-  if (e == hipSuccess) e = hipMalloc(&d_out, sizeof(SeriesOut) * nseries);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(d_desc, descs_host, sizeof(SeriesDesc) * nseries,
-                       hipMemcpyHostToDevice, st);
-  std::vector<SeriesOut> res(nseries);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_classify_series, dim3(nseries), dim3(kSeriesThreads), 0, st, d_desc,
-                       steady_tol, periodic_tol, min_lag, max_lag, d_work, stride, d_out);
-    e = hipGetLastError();
-  }
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(res.data(), d_out, sizeof(SeriesOut) * nseries, hipMemcpyDeviceToHost,
-                       st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess)
-    rc = lbm_fail(e == hipErrorOutOfMemory ? LBM_ENOMEM : LBM_EDEVICE, "classify: %s",
-                  hipGetErrorString(e));
-  if (d_desc) (void)hipFree(d_desc);
-  if (d_work) (void)hipFree(d_work);
-  if (d_out) (void)hipFree(d_out);
-  if (rc) return rc;
-  for (int s = 0; s < nseries; ++s) {
-    lbm_flow_state_t &o = out_host[s];
-    o.state = res[s].state;
-    o.lag = res[s].lag;
-    o.period = res[s].period;
-    o.amplitude = res[s].amplitude;
-    o.mean = res[s].mean;
-    o.std = res[s].std;
-    o.mismatch = res[s].mismatch;
-    o.cycle = res[s].cycle;
-    o.cycle_mismatch = res[s].cycle_mismatch;
-  }
-  return LBM_OK;
+  return classify_alloc([](const SeriesDesc *d) { return SeriesFromDesc{d}; }, descs_host,
+                        nseries, n, steady_tol, periodic_tol, min_lag, max_lag, st, out_host);
 }
 
 // Lag range check shared by the entry points.
@@ -84,10 +122,10 @@ int lbm_classify_series(const double *series_dev, int nseries, int64_t n, int64_
                     periodic_tol);
   int rc = check_lags(n, min_lag, max_lag);
   if (rc) return rc;
-  std::vector<SeriesDesc> d(nseries);
-  for (int s = 0; s < nseries; ++s) d[s] = SeriesDesc{series_dev + (long long)s * ld, n, 0, n, 1};
-  return classify_series_descs(d.data(), nseries, n, steady_tol, periodic_tol, min_lag, max_lag,
-                               (hipStream_t)hip_stream, out_host);
+  return classify_alloc(
+      [=](const SeriesDesc *) { return SeriesFromRows{series_dev, (long long)ld, (long long)n}; },
+      nullptr, nseries, n, steady_tol, periodic_tol, min_lag, max_lag, (hipStream_t)hip_stream,
+      out_host);
 }
 
 // ------------------------------------------------ no-allocation classifier
@@ -144,7 +182,7 @@ int lbm_classify_series_noalloc(const double *series_dev, int nseries, int64_t n
   int rc = check_lags(n, min_lag, max_lag);
   if (rc) return rc;
   // the same work layout as lbm_classify_series: the series, then its lags
-  const long long stride = 2 * (long long)n + 8;
+  const long long stride = series_work_doubles(n);
   if ((long long)nseries > kNoAllocScratchDoubles / stride)
     return lbm_fail(LBM_EINVAL,
                     "nseries * (2 n + 8) = %d * %lld doubles exceeds the %lld-double (32 MiB) "
@@ -153,10 +191,9 @@ int lbm_classify_series_noalloc(const double *series_dev, int nseries, int64_t n
                     nseries, stride, kNoAllocScratchDoubles);
   double *work = scratch_for_current_device(rc);
   if (!work) return rc;
-  hipLaunchKernelGGL(k_classify_strided<lbm_flow_state_t>, dim3(nseries), dim3(kSeriesThreads), 0,
-                     (hipStream_t)hip_stream, series_dev, (long long)n, (long long)ld, steady_tol,
-                     periodic_tol, min_lag, max_lag, work, stride, out_dev);
-  hipError_t e = hipGetLastError();
+  hipError_t e = launch_classify(SeriesFromRows{series_dev, (long long)ld, (long long)n}, nseries,
+                                 n, steady_tol, periodic_tol, min_lag, max_lag, work, stride,
+                                 out_dev, (hipStream_t)hip_stream);
   if (e != hipSuccess) return lbm_fail(LBM_EDEVICE, "classify launch: %s", hipGetErrorString(e));
   return LBM_OK;
 }
