@@ -260,23 +260,6 @@ __global__ __launch_bounds__(256) void k_canvas(const T *__restrict__ s, Geometr
   mask[k] = 1.f;
 }
 
-// Stream function: one thread per column, prefix sum of -u_x upward,
-// midpoint rule (Psi = 0 on the bottom wall).
-template <typename T, bool SHIFT>
-__global__ __launch_bounds__(256) void k_psi(const T *__restrict__ s, Geometry g,
-                                             double *__restrict__ psi) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= g.nx) return;
-  double acc = 0.0;
-  for (int y = 0; y < g.ny; ++y) {
-    double drho, jx, jy;
-    site_moments<T, SHIFT>(s, g.plane, y * g.pitch + x, drho, jx, jy);
-    const double ux = jx / (1.0 + drho);
-    psi[(size_t)y * g.nx + x] = -(acc + 0.5 * ux);
-    acc += ux;
-  }
-}
-
 // Store the equilibrium of Eq. 2 for fields rho, ux, uy (dense [ny][nx];
 // null rho = 1, null velocity = 0).  The equilibrium is its own collision
 // result, so this is the stored post-collision state of a start at

@@ -144,24 +144,4 @@ __global__ __launch_bounds__(256) void k_init_lid_row(T *__restrict__ d, Geometr
   for (int i = 0; i < 9; ++i) d[i * g.plane + o] = (T)e[i];
 }
 
-// Stream function on nodes: Psi = 0 on the bottom row, trapezoid rule up
-// each column, Psi[y] = Psi[y-1] - (u_x[y-1] + u_x[y]) / 2 (lattice units).
-template <typename T, bool SHIFT>
-__global__ __launch_bounds__(256) void k_psi_nodes(const T *__restrict__ s, Geometry g,
-                                                   double *__restrict__ psi) {
-  const int x = blockIdx.x * 256 + threadIdx.x;
-  if (x >= g.nx) return;
-  double drho, jx, jy;
-  site_moments<T, SHIFT>(s, g.plane, x, drho, jx, jy);
-  double prev = jx / (1.0 + drho), acc = 0.0;
-  psi[x] = 0.0;
-  for (int y = 1; y < g.ny; ++y) {
-    site_moments<T, SHIFT>(s, g.plane, y * g.pitch + x, drho, jx, jy);
-    const double ux = jx / (1.0 + drho);
-    acc = acc - 0.5 * (prev + ux);
-    psi[(size_t)y * g.nx + x] = acc;
-    prev = ux;
-  }
-}
-
 }  // namespace lbm

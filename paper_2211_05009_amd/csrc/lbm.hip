@@ -616,6 +616,28 @@ static void launch_moments_t(lbm_cavity *h, double *r, double *u, double *v) {
                      (const T *)h->buf[h->cur], geom(h), r, u, v);
 }
 
+// Blocks of k_psi (columns / kPsiCols).
+static int psi_blocks(const lbm_cavity *h) { return (h->nx + kPsiCols - 1) / kPsiCols; }
+
+template <typename T, bool S>
+static void launch_psi_t(lbm_cavity *h, double *psi, double *pv, int *pk, unsigned int *zero) {
+  const dim3 grid(psi_blocks(h)), block(kPsiThreads);
+  const T *src = (const T *)h->buf[h->cur];
+  const bool node = h->wall == LBM_WALL_NEE;
+  if (pv && node)
+    hipLaunchKernelGGL((k_psi<T, S, true, true>), grid, block, 0, h->stream, src, geom(h), psi,
+                       pv, pk, zero);
+  else if (pv)
+    hipLaunchKernelGGL((k_psi<T, S, true, false>), grid, block, 0, h->stream, src, geom(h), psi,
+                       pv, pk, zero);
+  else if (node)
+    hipLaunchKernelGGL((k_psi<T, S, false, true>), grid, block, 0, h->stream, src, geom(h), psi,
+                       pv, pk, zero);
+  else
+    hipLaunchKernelGGL((k_psi<T, S, false, false>), grid, block, 0, h->stream, src, geom(h), psi,
+                       pv, pk, zero);
+}
+
 // ------------------------------------------------------------------- C ABI
 extern "C" {
 
@@ -762,6 +784,7 @@ int lbm_destroy(lbm_t h) {
   if (h->mon_dev) (void)hipFree(h->mon_dev);
   if (h->aux_dev) (void)hipFree(h->aux_dev);
   if (h->mon_host) (void)hipHostFree(h->mon_host);
+  if (h->vortex_host) (void)hipHostFree(h->vortex_host);
   if (h->tmp) (void)hipFree(h->tmp);
   if (h->probe_xy) (void)hipFree(h->probe_xy);
   if (h->probe_ring) (void)hipFree(h->probe_ring);
@@ -1254,24 +1277,15 @@ int lbm_residual(lbm_t h, double *residual, int64_t *at_step) {
   return LBM_OK;
 }
 
-// Psi of the current state into the device array psi ([ny][nx] FP64).
-static int launch_psi(lbm_cavity *h, double *psi) {
-  if (h->wall == LBM_WALL_NEE) {
-    if (h->dtype == LBM_F64)
-      hipLaunchKernelGGL((k_psi_nodes<double, false>), dim3((h->nx + 255) / 256), dim3(256), 0,
-                         h->stream, (const double *)h->buf[h->cur], geom(h), psi);
-    else
-      hipLaunchKernelGGL((k_psi_nodes<float, true>), dim3((h->nx + 255) / 256), dim3(256), 0,
-                         h->stream, (const float *)h->buf[h->cur], geom(h), psi);
-    HIPC(hipGetLastError());
-    return LBM_OK;
-  }
+// Psi of the current state into the device array psi ([ny][nx] FP64); with
+// pv / pk also every block's best site of each vortex region; clears *zero
+// if not null.
+static int launch_psi(lbm_cavity *h, double *psi, double *pv = nullptr, int *pk = nullptr,
+                      unsigned int *zero = nullptr) {
   if (h->dtype == LBM_F64)
-    hipLaunchKernelGGL((k_psi<double, false>), dim3((h->nx + 255) / 256), dim3(256), 0,
-                       h->stream, (const double *)h->buf[h->cur], geom(h), psi);
+    launch_psi_t<double, false>(h, psi, pv, pk, zero);
   else
-    hipLaunchKernelGGL((k_psi<float, true>), dim3((h->nx + 255) / 256), dim3(256), 0,
-                       h->stream, (const float *)h->buf[h->cur], geom(h), psi);
+    launch_psi_t<float, true>(h, psi, pv, pk, zero);
   HIPC(hipGetLastError());
   return LBM_OK;
 }
@@ -1290,39 +1304,37 @@ int lbm_stream_function(lbm_t h, double *psi) {
 
 // ---------------------------------------------------------------- vortices
 namespace {
-// Views into h->tmp for the vortex routines: Psi, the per-block partials of
-// the three regions, the three results, the centre counter and up to `cap`
-// centres (value; site index and kind as an int pair).
+// Views into h->tmp for the vortex routines: what the host reads (the
+// extrema, the centre counter and up to `cap` centres), Psi, and the
+// per-block partials of the three regions.
 struct VortexScratch {
-  double *psi, *pv, *ov, *ev;
-  int *pk, *ok, *ek;
-  unsigned int *cnt;
+  VortexOut *out;
+  VortexCentre *list;
+  double *psi, *pv;
+  int *pk;
   int nb;
 };
 }  // namespace
 
 static int vortex_scratch(lbm_cavity *h, size_t cap, VortexScratch &s) {
   const size_t n = (size_t)h->nx * h->ny;
-  s.nb = (int)std::min<size_t>(1024, (n + kVortexThreads - 1) / kVortexThreads);
-  const size_t pk_doubles = (3 * (size_t)s.nb + 1) / 2;
-  int rc = ensure_tmp(h, n + 3 * s.nb + pk_doubles + 3 + 2 + 1 + 2 * cap);
+  static_assert(sizeof(VortexOut) == 40 && sizeof(VortexCentre) == 16, "whole doubles");
+  s.nb = psi_blocks(h);
+  int rc = ensure_tmp(h, 5 + 2 * cap + n + 3 * (size_t)s.nb + (3 * (size_t)s.nb + 1) / 2);
   if (rc) return rc;
   double *p = h->tmp;
+  s.out = reinterpret_cast<VortexOut *>(p);
+  p += 5;
+  s.list = reinterpret_cast<VortexCentre *>(p);
+  p += 2 * cap;
   s.psi = p;
   p += n;
   s.pv = p;
-  p += 3 * s.nb;
+  p += 3 * (size_t)s.nb;
   s.pk = reinterpret_cast<int *>(p);
-  p += pk_doubles;
-  s.ov = p;
-  p += 3;
-  s.ok = reinterpret_cast<int *>(p);
-  p += 2;
-  s.cnt = reinterpret_cast<unsigned int *>(p);
-  p += 1;
-  s.ev = p;
-  p += cap;
-  s.ek = reinterpret_cast<int *>(p);
+  if (!h->vortex_host)
+    HIPC(hipHostMalloc(&h->vortex_host, sizeof(VortexOut) + kVortexFirst * sizeof(VortexCentre),
+                       hipHostMallocDefault));
   return LBM_OK;
 }
 
@@ -1342,72 +1354,71 @@ static lbm_vortex_t vortex_record(const lbm_cavity *h, double psi, int k, int ki
   return v;
 }
 
-int lbm_vortex_extrema(lbm_t h, lbm_vortex_t *out) {
-  if (!h || !out) return lbm_fail(LBM_EINVAL, "NULL argument");
-  if (h->nx < 2) return lbm_fail(LBM_EINVAL, "nx = %d < 2", h->nx);
-  VortexScratch s;
-  int rc = vortex_scratch(h, 0, s);
-  if (rc) return rc;
-  rc = launch_psi(h, s.psi);
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_vortex_partial, dim3(s.nb), dim3(kVortexThreads), 0, h->stream, s.psi,
-                     h->nx, h->ny, s.pv, s.pk);
-  HIPC(hipGetLastError());
-  hipLaunchKernelGGL(k_vortex_final, dim3(1), dim3(kVortexThreads), 0, h->stream, s.pv, s.pk,
-                     s.nb, s.ov, s.ok);
-  HIPC(hipGetLastError());
-  double v[3];
-  int k[3];
-  HIPC(hipMemcpyAsync(v, s.ov, sizeof(v), hipMemcpyDeviceToHost, h->stream));
-  HIPC(hipMemcpyAsync(k, s.ok, sizeof(k), hipMemcpyDeviceToHost, h->stream));
-  HIPC(hipStreamSynchronize(h->stream));
-  for (int r = 0; r < 3; ++r) {
-    if (k[r] < 0) return lbm_fail(LBM_EDEVICE, "vortex region %d came back empty", r);
-    out[r] = vortex_record(h, v[r], k[r], r == 0 ? 1 : -1);
-  }
-  return LBM_OK;
-}
-
-// All vortex centres with |Psi| >= min_abs, sorted by site index.
-static int find_centres(lbm_cavity *h, double min_abs, std::vector<lbm_vortex_t> &all) {
+// Psi, then the extrema (ext) and / or all vortex centres with |Psi| >=
+// min_abs in row-major order (all), with one copy to the host and one wait
+// unless there are more than kVortexFirst centres.
+static int find_vortices(lbm_cavity *h, lbm_vortex_t *ext, double min_abs,
+                         std::vector<lbm_vortex_t> *all) {
   const size_t n = (size_t)h->nx * h->ny;
-  size_t cap = 4096;
+  size_t cap = all ? 4096 : 0;
   for (int pass = 0; pass < 2; ++pass) {
     VortexScratch s;
     int rc = vortex_scratch(h, cap, s);
     if (rc) return rc;
-    rc = launch_psi(h, s.psi);
+    rc = launch_psi(h, s.psi, ext ? s.pv : nullptr, s.pk, all ? &s.out->count : nullptr);
     if (rc) return rc;
-    HIPC(hipMemsetAsync(s.cnt, 0, sizeof(unsigned int), h->stream));
-    hipLaunchKernelGGL(k_vortex_centres, dim3((unsigned)((n + kVortexThreads - 1) / kVortexThreads)),
-                       dim3(kVortexThreads), 0, h->stream, s.psi, h->nx, h->ny, min_abs,
-                       (int)cap, s.cnt, s.ev, s.ek);
-    HIPC(hipGetLastError());
-    unsigned int cnt = 0;
-    HIPC(hipMemcpyAsync(&cnt, s.cnt, sizeof(cnt), hipMemcpyDeviceToHost, h->stream));
+    if (ext) {
+      hipLaunchKernelGGL(k_vortex_final, dim3(1), dim3(kVortexThreads), 0, h->stream, s.pv, s.pk,
+                         s.nb, s.out);
+      HIPC(hipGetLastError());
+    }
+    if (all) {
+      hipLaunchKernelGGL(k_vortex_centres,
+                         dim3((unsigned)((n + kVortexThreads - 1) / kVortexThreads)),
+                         dim3(kVortexThreads), 0, h->stream, s.psi, h->nx, h->ny, min_abs,
+                         (int)cap, &s.out->count, s.list);
+      HIPC(hipGetLastError());
+    }
+    VortexOut *got = static_cast<VortexOut *>(h->vortex_host);
+    HIPC(hipMemcpyAsync(got, s.out,
+                        sizeof(VortexOut) + (all ? kVortexFirst * sizeof(VortexCentre) : 0),
+                        hipMemcpyDeviceToHost, h->stream));
     HIPC(hipStreamSynchronize(h->stream));
+    if (ext)
+      for (int r = 0; r < kVortexRegions; ++r) {
+        if (got->k[r] < 0) return lbm_fail(LBM_EDEVICE, "vortex region %d came back empty", r);
+        ext[r] = vortex_record(h, got->v[r], got->k[r], r == 0 ? 1 : -1);
+      }
+    if (!all) return LBM_OK;
+    const unsigned int cnt = got->count;
     if (cnt > cap) {   // more centres than slots: run again with room for all
       cap = cnt;
       continue;
     }
-    std::vector<double> ev(cnt);
-    std::vector<int> ek(2 * (size_t)cnt);
-    if (cnt) {
-      HIPC(hipMemcpyAsync(ev.data(), s.ev, cnt * sizeof(double), hipMemcpyDeviceToHost,
+    const VortexCentre *c = reinterpret_cast<const VortexCentre *>(got + 1);
+    std::vector<VortexCentre> more;
+    if (cnt > (unsigned int)kVortexFirst) {
+      more.resize(cnt);
+      HIPC(hipMemcpyAsync(more.data(), s.list, cnt * sizeof(VortexCentre), hipMemcpyDeviceToHost,
                           h->stream));
-      HIPC(hipMemcpyAsync(ek.data(), s.ek, 2 * (size_t)cnt * sizeof(int),
-                          hipMemcpyDeviceToHost, h->stream));
       HIPC(hipStreamSynchronize(h->stream));
+      c = more.data();
     }
-    all.clear();
+    all->clear();
     for (unsigned int i = 0; i < cnt; ++i)
-      all.push_back(vortex_record(h, ev[i], ek[2 * i], ek[2 * i + 1]));
-    std::sort(all.begin(), all.end(), [](const lbm_vortex_t &a, const lbm_vortex_t &b) {
+      all->push_back(vortex_record(h, c[i].psi, c[i].k, c[i].kind));
+    std::sort(all->begin(), all->end(), [](const lbm_vortex_t &a, const lbm_vortex_t &b) {
       return a.iy != b.iy ? a.iy < b.iy : a.ix < b.ix;
     });
     return LBM_OK;
   }
   return lbm_fail(LBM_EDEVICE, "vortex centre count changed between two scans");
+}
+
+int lbm_vortex_extrema(lbm_t h, lbm_vortex_t *out) {
+  if (!h || !out) return lbm_fail(LBM_EINVAL, "NULL argument");
+  if (h->nx < 2) return lbm_fail(LBM_EINVAL, "nx = %d < 2", h->nx);
+  return find_vortices(h, out, 0.0, nullptr);
 }
 
 int lbm_vortex_centres(lbm_t h, double min_abs_psi, int cap, lbm_vortex_t *out, int *count) {
@@ -1416,7 +1427,7 @@ int lbm_vortex_centres(lbm_t h, double min_abs_psi, int cap, lbm_vortex_t *out, 
     return lbm_fail(LBM_EINVAL, "cap = %d with out = %p", cap, (void *)out);
   if (!(min_abs_psi >= 0.0)) return lbm_fail(LBM_EINVAL, "min_abs_psi = %g", min_abs_psi);
   std::vector<lbm_vortex_t> all;
-  int rc = find_centres(h, min_abs_psi, all);
+  int rc = find_vortices(h, nullptr, min_abs_psi, &all);
   if (rc) return rc;
   *count = (int)all.size();
   for (int i = 0; i < cap && i < (int)all.size(); ++i) out[i] = all[i];
@@ -1427,10 +1438,8 @@ int lbm_bottom_vortex_count(lbm_t h, double min_abs_psi, int *count) {
   if (!h || !count) return lbm_fail(LBM_EINVAL, "NULL argument");
   if (!(min_abs_psi >= 0.0)) return lbm_fail(LBM_EINVAL, "min_abs_psi = %g", min_abs_psi);
   lbm_vortex_t ext[3];
-  int rc = lbm_vortex_extrema(h, ext);
-  if (rc) return rc;
   std::vector<lbm_vortex_t> all;
-  rc = find_centres(h, min_abs_psi, all);
+  int rc = find_vortices(h, ext, min_abs_psi, &all);
   if (rc) return rc;
   int c = 0;
   for (const lbm_vortex_t &v : all) c += v.iy < ext[0].iy;

@@ -68,6 +68,7 @@ struct lbm_cavity {
   double *mon_dev = nullptr;    // chunk monitor sums: sum(rho-1), num, den
   double *aux_dev = nullptr;    // on-demand reductions
   double *mon_host = nullptr;   // pinned
+  void *vortex_host = nullptr;  // pinned results of a vortex call, from its first use on
   double *tmp = nullptr;        // FP64 transfer scratch
   size_t tmp_doubles = 0;
   // probe time series
