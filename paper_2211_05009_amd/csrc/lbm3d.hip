@@ -24,6 +24,37 @@ namespace {
 // 4-7 a TX x TY column marching through z (k_step3_zs2; FP32 64 x 8,
 // 64 x 12, 32 x 16, 32 x 24; FP64 32 x 12, 32 x 8, 16 x 16, 24 x 16)
 constexpr int kNum3Variants = 8;
+// The shape a new handle starts with (lbm3d_autotune refines it).  The
+// two-step shapes read and write the state once for two steps; what they cost
+// on a small box is the last, partly filled round of blocks (one block per CU).
+// Measured on one MI355X, us per step, one-step shape 1 / shape 3 / shape 4:
+//   FP32: 48 x 40 x 64  6.6 / 4.4 / 6.2     96^3          23.1 / 18.9 / 21.9
+//         64^3          8.4 / 5.8 / 7.1     128^3         63.6 / 49.8 / 41.1
+//         40 x 150 x 60 13.6 / 13.3 / 13.4  256^3         516 / 407 / 293
+//   FP64: 32^3          5.7 / 3.9 / 5.9     64 x 64 x 192 36.2 / 35.0 / 34.7
+//         48 x 40 x 64  8.7 / 7.4 / 8.1     96^3          58.5 / 41.3 / 36.2
+//         180 x 33 x 33 10.8 / 12.2 / 11.7  192^3         418 / 344 / 245
+// So: columns marching through z (4) on a box that streams from the memory
+// behind the caches, from 1.2 M sites in FP32 and 0.7 M in FP64; below that
+// the 3-D tile (3), in FP64 only while its tiles take at most two rounds of
+// the 256 CUs (its 16 x 6 x 4 tiles recompute 2.25 of every site, and the
+// one-step shape ties or wins from the third round on).  A box so thin that
+// its sites fill less than 40 % of the tiles stays with the one-step shape.
+int default_shape3(int nx, int ny, int nz, int dtype) {
+  const bool f64 = dtype == LBM_F64;
+  const long long n = (long long)nx * ny * nz;
+  auto tiles = [&](int tx, int ty, int tz) {
+    return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
+  };
+  if (n >= (f64 ? 700000 : 1200000)) {
+    const int tx = f64 ? 32 : 64, ty = f64 ? 12 : 8;
+    return 5 * n >= 2 * tiles(tx, ty, 1) * tx * ty ? 4 : 1;
+  }
+  const int tx = f64 ? 16 : 32, ty = f64 ? 6 : 8, tz = 4;
+  const long long nt = tiles(tx, ty, tz);
+  return 5 * n >= 2 * nt * tx * ty * tz && (!f64 || nt <= 512) ? 3 : 1;
+}
+
 // blocks of the monitor and mass reductions (each thread takes a few sites:
 // more waves in flight than the two-dimensional handles' 1024 blocks give)
 constexpr int kRed3Blocks = 8192;
@@ -342,6 +373,7 @@ int lbm3d_create(int nx, int ny, int nz, double re, double u_lid, int dtype, lbm
   h->u_lid = u_lid;
   h->tau = tau;
   h->omega = 1.0 / tau;
+  h->variant = default_shape3(nx, ny, nz, dtype);
   const size_t esz = dtype == LBM_F64 ? 8 : 4;
   h->buf_bytes = (size_t)plane * 19 * esz;
   auto bail = [&](int code) {
