@@ -127,17 +127,15 @@ void tune_cache_store(const std::string &key, int variant) {
 // ---------------------------------------------------------------- variants
 // Step kernel variants.  Scalar (k_step): tile 64 x (BY*RY) sites, block
 // 64 x BY threads.  Vector (k_step_vec): tile (64 V) x BY sites, V = 16 B /
-// element, block 64 x BY.  Temporal (k_step_tb, variants 12-23): K steps per
+// element, block 64 x BY.  Temporal (k_step_tb, variants 12-32): K steps per
 // launch on TX x TY tiles held in LDS.  All give bit-identical results.
-static const int kNumVariants = 29;
-// K = 5 steps per launch on 32 x 32 tiles, 1024 threads: the fastest shape
-// on the 500 x (500 Ar) lattices on gfx950 (lbm_autotune refines it).
-static const int kDefaultVariant = 22;
+static const int kNumVariants = 33;
 
 // Steps applied by one launch of variant v.
 static int steps_per_launch(int v) {
   static const int k[kNumVariants] = {1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 1, 4, 4, 2,
-                                      5, 4, 4, 5, 5, 10, 10, 5, 5, 5, 4, 5, 5, 5};
+                                      5, 4, 4, 5, 5, 10, 10, 5, 5, 5, 4, 5, 5, 5,
+                                      5, 5, 5, 5};
   return (v >= 0 && v < kNumVariants) ? k[v] : 1;
 }
 
@@ -146,9 +144,10 @@ static int steps_per_launch(int v) {
 // multi-step shapes).
 static void tile_of(int v, int dtype, int &tx, int &ty) {
   static const int one[8] = {4, 8, 16, 8, 8, 8, 16, 16};   // k_step: 64 x (BY RY)
-  static const int tb[17][2] = {{32, 32}, {32, 32}, {32, 32}, {32, 32}, {64, 16}, {16, 16},
+  static const int tb[21][2] = {{32, 32}, {32, 32}, {32, 32}, {32, 32}, {64, 16}, {16, 16},
                                 {64, 16}, {16, 16}, {32, 32}, {64, 32}, {32, 32}, {64, 32},
-                                {32, 32}, {32, 32}, {32, 16}, {32, 48}, {32, 64}};
+                                {32, 32}, {32, 32}, {32, 16}, {32, 48}, {32, 64}, {8, 8},
+                                {24, 16}, {32, 16}, {32, 16}};
   const bool f64 = dtype == LBM_F64;
   if (v < 8) {
     tx = 64;
@@ -165,6 +164,45 @@ static void tile_of(int v, int dtype, int &tx, int &ty) {
     if (f64 && (v == 24 || v == 25)) tx = ty = 16;
     if (f64 && (v == 27 || v == 28)) tx = 16;
   }
+}
+
+// The shape a new half-way handle starts with (lbm_autotune refines it): K =
+// 5 everywhere, so that the calls and probe cadences that take K-step
+// launches do not depend on the lattice.  A launch on a small lattice is a
+// chain of latencies (step 1's loads, four barriers, the stores) during which
+// most CUs have nothing to do, so small tiles with one window site per thread
+// and two LDS buffers win although they recompute more halo; once the tiles
+// fill the CUs, larger tiles do.  Measured on one MI355X, us per step over
+// graph-replayed launches (T = the tiles of the shape in question):
+//   8 x 8 (29) against 24 x 16 (30): FP32 64^2 (T = 64) 0.85 / 1.07, 200^2
+//     (625) 1.00 / 1.06, 257^2 (1089) 1.15 / 1.11; FP64 64^2 0.92 / 1.24,
+//     200^2 1.23 / 1.38, 257^2 1.68 / 1.44; all took 1.6-1.75 / 2.2-2.4 with
+//     32 x 32 (22);
+//   24 x 16 (30) against 32 x 16 (31): FP32 200 x 400 (225) 1.12 / 1.19, 500 x
+//     200 (273) 1.25 / 1.22; FP64 200 x 400 1.46 / 1.57, 500 x 200 1.97 / 1.56;
+//   FP32 24 x 16 (30) against 32 x 32 in two buffers (24): 400^2 (425) 1.45 /
+//     1.64, 500^2 (672) 1.89 / 1.66 (22: 1.81);
+//   FP32 32 x 16 (31) against 22: 500 x 750 (752) 2.40 / 2.74, 500 x 1000 (1008)
+//     2.98 / 2.82;
+//   FP64 32 x 16 in one buffer (32) against 22: 300 x 500 2.29 / 2.35, 500^2
+//     2.70 / 2.76, 500 x 1000 4.74 / 5.27, 1024^2 9.4 / 10.4;
+//   beyond the caches 64 x 16 in FP32 (18) against 22: 1500 x 1200 8.97 / 8.76,
+//     2048^2 18.8 / 20.3, 4096^2 66 / 76; 32 x 16 with 512 threads in FP64
+//     (26) against 960 (32): 1500 x 1200 16.3 / 16.2, 2048^2 33.4 / 35.8, 4096^2
+//     127 / 142 (22: 186).
+static int default_variant(int nx, int ny, int dtype) {
+  auto tiles = [&](int tx, int ty) {
+    return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+  };
+  if (tiles(8, 8) <= 640) return 29;
+  if (tiles(24, 16) <= 256) return 30;
+  if (tiles(32, 16) <= 256) return 31;
+  const bool large = (long long)nx * ny >= 3000000;
+  if (dtype == LBM_F64) return large ? 26 : 32;
+  if (tiles(24, 16) <= 448) return 30;
+  if (tiles(32, 32) <= 256) return 24;
+  if (tiles(32, 16) <= 768) return 31;
+  return large ? 18 : 22;
 }
 
 // Non-equilibrium extrapolation handles have their own shapes: four
@@ -346,7 +384,7 @@ static hipError_t launch_tb_t(const lbm_cavity *h, const void *src, void *dst,
   return hipGetLastError();
 }
 
-// mon applies to the multi-step shapes (12-23) only.
+// mon applies to the multi-step shapes (12 on) only.
 template <typename T, bool S>
 static hipError_t launch_step_variant(const lbm_cavity *h, int v, const void *src,
                                       void *dst, hipStream_t st, int mon) {
@@ -404,6 +442,11 @@ static hipError_t launch_step_variant(const lbm_cavity *h, int v, const void *sr
         return launch_tb_t<T, S, 5, 16, 64, 512>(h, src, dst, st, mon);
       else
         return launch_tb_t<T, S, 5, 32, 64, 1024>(h, src, dst, st, mon);
+    // one window site per thread at step 1 or close to it (default_variant)
+    case 29: return launch_tb_t<T, S, 5, 8, 8, 256, true>(h, src, dst, st, mon);
+    case 30: return launch_tb_t<T, S, 5, 24, 16, 768, true>(h, src, dst, st, mon);
+    case 31: return launch_tb_t<T, S, 5, 32, 16, 960, true>(h, src, dst, st, mon);
+    case 32: return launch_tb_t<T, S, 5, 32, 16, 960>(h, src, dst, st, mon);
     case 0: return launch_step_t<T, S, 4, 1>(h, src, dst, st);
     case 1: return launch_step_t<T, S, 4, 2>(h, src, dst, st);
     case 2: return launch_step_t<T, S, 4, 4>(h, src, dst, st);
@@ -679,7 +722,7 @@ static int create_impl(int nx, int ny, double tau, double re, double u_lid,
   h->u_lid = u_lid;
   h->tau = tau;
   h->omega = 1.0 / tau;
-  h->variant = wall == LBM_WALL_NEE ? kDefaultNeeVariant : kDefaultVariant;
+  h->variant = wall == LBM_WALL_NEE ? kDefaultNeeVariant : default_variant(nx, ny, dtype);
   h->use_graph = 1;
   const size_t esz = dtype == LBM_F64 ? 8 : 4;
   h->buf_bytes = (size_t)plane * 9 * esz;
@@ -706,8 +749,8 @@ static int create_impl(int nx, int ny, double tau, double re, double u_lid,
   }
   TRY(hipMalloc(&h->uref, sizeof(double2) * (size_t)nx * ny));
   // partial sums: the monitor's fixed grid, or one triple per tile of the
-  // smallest multi-step tile (16 x 16) for the fused monitor
-  h->partial_slots = std::max(kRedBlocks, ((nx + 15) / 16) * ((ny + 15) / 16));
+  // smallest multi-step tile (8 x 8) for the fused monitor
+  h->partial_slots = std::max(kRedBlocks, ((nx + 7) / 8) * ((ny + 7) / 8));
   TRY(hipMalloc(&h->partials, sizeof(double) * kNumSums * (size_t)h->partial_slots));
   TRY(hipMalloc(&h->mon_dev, sizeof(double) * 4));
   TRY(hipMalloc(&h->aux_dev, sizeof(double) * 4));

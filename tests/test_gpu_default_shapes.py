@@ -40,3 +40,29 @@ def test_box(lbm, dtype, box, shape):
         got.append(c.get_populations())
     assert np.array_equal(got[0], got[1])
     c.close()
+
+
+@pytest.mark.parametrize("dtype,nx,ny,shape", [
+    ("f32s", 2, 2, 29), ("f64", 200, 200, 29), ("f32s", 201, 200, 30),   # 640 tiles of 8 x 8
+    ("f64", 384, 256, 30), ("f64", 385, 256, 31), ("f32s", 384, 272, 31),  # 256 of 24 x 16
+    ("f64", 500, 256, 31), ("f64", 513, 256, 32),                        # 256 of 32 x 16
+    ("f32s", 384, 448, 30), ("f32s", 385, 448, 24),                      # 448 of 24 x 16
+    ("f32s", 512, 512, 24), ("f32s", 513, 512, 31),                      # 256 of 32 x 32
+    ("f32s", 768, 513, 22),                                              # 768 of 32 x 16
+    ("f32s", 1750, 1715, 18), ("f64", 1750, 1715, 26),                   # 3 M sites
+])
+def test_cavity(lbm, dtype, nx, ny, shape):
+    rng = np.random.default_rng(nx)
+    w = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)
+    f = w[:, None, None] + rng.uniform(-4e-3, 4e-3, (9, ny, nx))
+    c = lbm.Cavity(nx, ny, tau=0.56, u_lid=U_LID, dtype=dtype)
+    assert c.get_option(lbm.LBM_OPT_STEP_VARIANT) == shape
+    got = []
+    for v in (shape, 0):
+        c.set_option(lbm.LBM_OPT_STEP_VARIANT, v)
+        c.set_populations(f)
+        c.step(117)
+        got.append((c.get_populations(), c.residual()[0]))
+    assert np.array_equal(got[0][0], got[1][0])
+    assert abs(got[0][1] - got[1][1]) <= 1e-12 * got[1][1]
+    c.close()
