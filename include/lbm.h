@@ -127,9 +127,9 @@ int lbm_create_tau(int nx, int ny, double tau, double u_lid, int dtype,
  * is the trapezoid rule up each column from Psi = 0 on the bottom row.  NEE
  * handles have LBM_OPT_NUM_VARIANTS = 8 tile shapes: 0-3 take one step per
  * launch (64 x {4, 8} nodes), 4-7 take K steps per launch on a tile kept
- * in LDS (16 x 16, K = 4; 32 x 16, K = 5, FP64 16 x 16; 32 x 32, K = 4,
- * FP64 16 x 32; 32 x 32, K = 5, FP64 16 x 32 with K = 2).  Every shape
- * gives the same bits.
+ * in LDS (16 x 16, K = 4; 32 x 16, K = 5, FP64 16 x 16; K = 4 on a tile
+ * of 8 x 8 to 32 x 32 chosen from the lattice, LBM_OPT_TILE_X and _Y; 32 x 32,
+ * K = 5, FP64 16 x 32 with K = 2).  Every shape gives the same bits.
  * Errors: as lbm_create; LBM_EINVAL for an unknown wall, or NEE with nx or
  * ny < 3.
  */

@@ -208,12 +208,39 @@ static int default_variant(int nx, int ny, int dtype) {
 // Non-equilibrium extrapolation handles have their own shapes: four
 // one-step ones (k_step_nee, 64 x (BY RY) nodes) and four multi-step ones
 // (k_step_nee_tb): 16 x 16, K = 4; K = 5 on 32 x 16 (FP64 16 x 16); K = 4
-// on 32 x 32 (FP64 16 x 32); K = 5 on 32 x 32 (FP64 K = 2 on 16 x 32).
+// on a tile chosen from the lattice (nee_tile6); K = 5 on 32 x 32 (FP64 K = 2
+// on 16 x 32).
 static const int kNumNeeVariants = 8;
-// default NEE shape before lbm_autotune: within 5 % of the best at 501^2
-// in both precisions and the best in FP64 at 257^2 (FP32 at 257^2: 30
-// against 36 GLUPS for shape 5)
 static const int kDefaultNeeVariant = 6;
+
+// Tile of NEE shape 6 (K = 4, two LDS buffers, one site of the first window
+// per thread or close to it): small tiles while the lattice leaves CUs idle,
+// as default_variant chooses for the half-way walls.  us per step over
+// graph-replayed launches on one MI355X (T = tiles of the shape in question):
+//   8 x 8 against 16 x 16: FP32 64^2 (T = 64) 0.93 / 1.01, 150^2 (361) 1.07 /
+//     1.06, 200^2 (625) 1.17 / 1.11; FP64 64^2 1.05 / 1.29, 150^2 1.24 / 1.37,
+//     200^2 1.43 / 1.43;
+//   24 x 16 against 32 x 16: FP32 257^2 (187) 1.23 / 1.32, 400^2 (425) 1.63 /
+//     1.77; FP64 257^2 1.65 / 1.79, 400^2 2.77 / 3.05; but 500 x 200 (273)
+//     1.53 / 1.36, FP64 2.54 / 1.89, where 32 x 16 fits the 256 CUs in one round;
+//   FP32 32 x 16 against 32 x 32: 500^2 (512) 1.91 / 1.85, 500 x 750 (752)
+//     2.51 / 3.0, 500 x 1000 (1008) 3.42 / 3.41;
+//   FP64 32 x 16 with 960 threads against 16 x 32 with 512, this shape's tile
+//     before: 500^2 3.33 / 3.68, 500 x 1000 6.13 / 6.76, 1024^2 12.0 / 13.3.
+enum NeeTile { kNee8x8, kNee16x16, kNee24x16, kNee32x16, kNee32x32 };
+static NeeTile nee_tile6(int nx, int ny, int dtype) {
+  auto tiles = [&](int tx, int ty) {
+    return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+  };
+  if (tiles(8, 8) <= 400) return kNee8x8;
+  if (tiles(16, 16) <= 256) return kNee16x16;
+  if (tiles(24, 16) <= 256) return kNee24x16;
+  if (tiles(32, 16) <= 256) return kNee32x16;
+  if (tiles(24, 16) <= 448) return kNee24x16;
+  if (dtype == LBM_F64) return kNee32x16;
+  if (tiles(32, 32) <= 256) return kNee32x32;
+  return tiles(32, 16) <= 768 ? kNee32x16 : kNee32x32;
+}
 
 static int num_variants(const lbm_cavity *h) {
   return h->wall == LBM_WALL_NEE ? kNumNeeVariants : kNumVariants;
@@ -229,9 +256,10 @@ static int launch_steps(const lbm_cavity *h, int v) {
 }
 
 // Tile (nodes along x, along y) of NEE variant v.
-static void nee_tile_of(int v, int dtype, int &tx, int &ty) {
+static void nee_tile_of(const lbm_cavity *h, int v, int &tx, int &ty) {
   static const int one[4] = {4, 8, 8, 8};   // k_step_nee: 64 x (BY RY)
-  const bool f64 = dtype == LBM_F64;
+  static const int six[5][2] = {{8, 8}, {16, 16}, {24, 16}, {32, 16}, {32, 32}};
+  const bool f64 = h->dtype == LBM_F64;
   if (v >= 0 && v < 4) {
     tx = 64;
     ty = one[v];
@@ -240,7 +268,11 @@ static void nee_tile_of(int v, int dtype, int &tx, int &ty) {
   } else if (v == 5) {
     tx = f64 ? 16 : 32;
     ty = 16;
-  } else {   // shapes 6 and 7
+  } else if (v == 6) {
+    const NeeTile k = nee_tile6(h->nx, h->ny, h->dtype);
+    tx = six[k][0];
+    ty = six[k][1];
+  } else {
     tx = f64 ? 16 : 32;
     ty = 32;
   }
@@ -301,10 +333,15 @@ static hipError_t launch_nee_variant(const lbm_cavity *h, int v, const void *src
       else
         return launch_nee_tb_t<T, S, 5, 32, 16, 512>(h, src, dst, st);
     case 6:
-      if constexpr (f64)
-        return launch_nee_tb_t<T, S, 4, 16, 32, 512>(h, src, dst, st);
-      else
-        return launch_nee_tb_t<T, S, 4, 32, 32, 1024>(h, src, dst, st);
+      switch (nee_tile6(h->nx, h->ny, h->dtype)) {
+        case kNee8x8: return launch_nee_tb_t<T, S, 4, 8, 8, 256>(h, src, dst, st);
+        case kNee16x16: return launch_nee_tb_t<T, S, 4, 16, 16, 576>(h, src, dst, st);
+        case kNee24x16: return launch_nee_tb_t<T, S, 4, 24, 16, 768>(h, src, dst, st);
+        case kNee32x16: return launch_nee_tb_t<T, S, 4, 32, 16, 960>(h, src, dst, st);
+        default:
+          if constexpr (!f64) return launch_nee_tb_t<T, S, 4, 32, 32, 1024>(h, src, dst, st);
+          return hipErrorInvalidValue;   // FP64 takes no 32 x 32 tile
+      }
     case 7:
       if constexpr (f64)
         return launch_nee_tb_t<T, S, 2, 16, 32, 512>(h, src, dst, st);
@@ -895,7 +932,7 @@ int lbm_get_option(lbm_t h, int option, int64_t *value) {
     case LBM_OPT_TILE_Y: {
       int tx = 64, ty = 4;
       if (h->wall == LBM_WALL_NEE) {
-        nee_tile_of(h->variant, h->dtype, tx, ty);
+        nee_tile_of(h, h->variant, tx, ty);
       } else {
         tile_of(h->variant, h->dtype, tx, ty);
       }

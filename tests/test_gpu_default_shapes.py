@@ -66,3 +66,29 @@ def test_cavity(lbm, dtype, nx, ny, shape):
     assert np.array_equal(got[0][0], got[1][0])
     assert abs(got[0][1] - got[1][1]) <= 1e-12 * got[1][1]
     c.close()
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32s"])
+@pytest.mark.parametrize("nx,ny,tile", [
+    (3, 3, (8, 8)), (160, 160, (8, 8)), (161, 160, (16, 16)),      # 400 tiles of 8 x 8
+    (256, 256, (16, 16)), (257, 256, (24, 16)),                    # 256 of 16 x 16
+    (385, 256, (32, 16)), (513, 256, (24, 16)),                    # 256 of 24 x 16, 32 x 16
+    (385, 449, None), (513, 513, None), (768, 529, None),          # by storage type
+])
+def test_nee(lbm, dtype, nx, ny, tile):
+    if tile is None:
+        tile = (32, 16) if dtype == "f64" or nx == 513 else (32, 32)
+    rng = np.random.default_rng(nx)
+    w = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)
+    f = w[:, None, None] + rng.uniform(-4e-3, 4e-3, (9, ny, nx))
+    c = lbm.Cavity(nx, ny, re=2.0 * nx, u_lid=U_LID, dtype=dtype, wall="nee")
+    assert c.get_option(lbm.LBM_OPT_STEP_VARIANT) == 6
+    assert (c.get_option(lbm.LBM_OPT_TILE_X), c.get_option(lbm.LBM_OPT_TILE_Y)) == tile
+    got = []
+    for v in (6, 0):
+        c.set_option(lbm.LBM_OPT_STEP_VARIANT, v)
+        c.set_populations(f)
+        c.step(117)
+        got.append(c.get_populations())
+    assert np.array_equal(got[0], got[1])
+    c.close()
