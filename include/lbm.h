@@ -499,7 +499,8 @@ int lbm_load(lbm_t h, const char *path);
  * same arguments (bit for bit: the per-site arithmetic is the same).
  * Steps are applied to the *active* cavities; inactive ones keep their state
  * and step count.  Monitors (mass, Eq. 6) run per cavity every 100 batch
- * steps; aligned runs of LBM_OPT_GRAPH_STEPS steps replay a HIP graph.
+ * steps; aligned runs of LBM_OPT_GRAPH_STEPS steps, and 100-step chunks of
+ * what is left, replay HIP graphs.
  * Cavity indices k are 0-based; out-of-range k gives LBM_EINVAL.
  * ---------------------------------------------------------------------- */
 typedef struct lbm_batch *lbm_batch_t;

@@ -63,7 +63,8 @@ struct lbm_batch {
   double threshold = 0.0;
   int variant = 12, use_graph = 1, graph_steps = 1000;   // 12: K = 5 on 32 x 32 tiles
   hipStream_t stream = nullptr, own_stream = nullptr, cap_stream = nullptr;
-  hipGraphExec_t graph = nullptr;
+  hipGraphExec_t graph = nullptr;       // graph_steps steps
+  hipGraphExec_t graph1 = nullptr;      // one 100-step chunk, for calls that do not fill those
   bool tables_dirty = true;
   // probe time series, recorded at every monitor of an active cavity
   double *probe_xy = nullptr;                 // [n][probe_n][2]
@@ -233,8 +234,10 @@ Geometry cav_geom(const lbm_batch *b, int k) {
 }
 
 void drop_graph(lbm_batch *b) {
-  if (b->graph) (void)hipGraphExecDestroy(b->graph);
-  b->graph = nullptr;
+  for (hipGraphExec_t *g : {&b->graph, &b->graph1}) {
+    if (*g) (void)hipGraphExecDestroy(*g);
+    *g = nullptr;
+  }
 }
 
 // Rebuild the step / monitor tile tables for the active cavities.
@@ -312,24 +315,24 @@ int rebuild_tables(lbm_batch *b) {
   return LBM_OK;
 }
 
-// graph_steps steps from a monitored state at a multiple of 100, ending
-// with every cavity's monitor of each later multiple of 100.  Multi-step
+// `steps` steps (a multiple of 100) from a monitored state at a multiple of
+// 100, ending with every cavity's monitor of each later multiple of 100.  Multi-step
 // shapes carry the monitor of a chunk's start state in the chunk's first
 // two launches (k_step_batch_tb, MON = 1 and 2) from the second chunk on,
 // and the state the graph ends in gets the separate pass, which the host
 // reads.  Probe series are recorded by the separate pass, so with probes
 // every chunk ends with it.
-hipError_t issue_chunk(lbm_batch *b, hipStream_t st) {
+hipError_t issue_chunk(lbm_batch *b, int steps, hipStream_t st) {
   const int K = shape_steps(b->variant);
   const bool fused = kShapes[b->variant].kind == 2 && b->probe_n == 0;
   int cur = 0;
-  for (int k = K; k <= b->graph_steps; k += K) {
+  for (int k = K; k <= steps; k += K) {
     const int done = (k - K) % kChunk;   // steps of this chunk before the launch
     const int mon = (fused && k > kChunk) ? (done == 0 ? 1 : done == K ? 2 : 0) : 0;
     hipError_t e = batch_launch(b, cur, st, mon);
     if (e != hipSuccess) return e;
     cur = 1 - cur;
-    if (k % kChunk == 0 && (!fused || k == b->graph_steps)) {
+    if (k % kChunk == 0 && (!fused || k == steps)) {
       e = batch_monitor(b, cur, st);
       if (e != hipSuccess) return e;
     }
@@ -337,20 +340,20 @@ hipError_t issue_chunk(lbm_batch *b, hipStream_t st) {
   return hipSuccess;
 }
 
-int build_graph(lbm_batch *b) {
+int build_graph(lbm_batch *b, int steps, hipGraphExec_t &exec) {
   hipGraph_t g = nullptr;
   HIPC(hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t e = issue_chunk(b, b->cap_stream);
+  hipError_t e = issue_chunk(b, steps, b->cap_stream);
   hipError_t e2 = hipStreamEndCapture(b->cap_stream, &g);
   if (e != hipSuccess || e2 != hipSuccess) {
     if (g) (void)hipGraphDestroy(g);
     return lbm_fail(LBM_EDEVICE, "batch graph capture failed: %s",
                     hipGetErrorString(e != hipSuccess ? e : e2));
   }
-  e = hipGraphInstantiate(&b->graph, g, nullptr, nullptr, 0);
+  e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
   (void)hipGraphDestroy(g);
   if (e != hipSuccess) {
-    b->graph = nullptr;
+    exec = nullptr;
     return lbm_fail(LBM_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
   }
   return LBM_OK;
@@ -683,24 +686,28 @@ static int batch_step_impl(lbm_batch_t b, int64_t n) {
     }
     if (b->ntiles == 0) break;       // every cavity inactive
     const bool aligned = b->t_global % kChunk == 0;
-    if (aligned && n >= b->graph_steps) {
+    if (aligned && n >= kChunk) {
+      // whole graphs of graph_steps steps, then 100-step chunks (a call of
+      // 500 steps of the 25-cavity sweep took 500 one-step launches)
+      const int steps = n >= b->graph_steps ? b->graph_steps : kChunk;
       if (b->use_graph) {
-        if (!b->graph) {
-          int rc = build_graph(b);
+        hipGraphExec_t &exec = steps == b->graph_steps ? b->graph : b->graph1;
+        if (!exec) {
+          int rc = build_graph(b, steps, exec);
           if (rc) return rc;
         }
-        HIPC(hipGraphLaunch(b->graph, b->stream));
+        HIPC(hipGraphLaunch(exec, b->stream));
       } else {
-        hipError_t e = issue_chunk(b, b->stream);
+        hipError_t e = issue_chunk(b, steps, b->stream);
         if (e != hipSuccess) return lbm_fail(LBM_EDEVICE, "batch chunk: %s", hipGetErrorString(e));
       }
-      for (int k = 0; k < b->graph_steps / kChunk; ++k) {
+      for (int k = 0; k < steps / kChunk; ++k) {
         for (int c = 0; c < b->n; ++c)
           if (b->active[c]) b->t[c] += kChunk;
         b->t_global += kChunk;
         note_monitor(b);
       }
-      n -= b->graph_steps;
+      n -= steps;
       monitored = true;
     } else {
       hipError_t e = batch_step1(b, b->cur, b->stream);

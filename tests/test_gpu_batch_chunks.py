@@ -1,0 +1,61 @@
+"""Batch calls that do not fill a captured graph: 100-step chunks, then single
+steps, against single cavities of one-step shapes: populations bit for bit,
+Eq. 6 within 1e-12 relative, and the threshold checked at every monitor."""
+import numpy as np
+import pytest
+
+from cavity_inputs import U_LID, random_shift
+
+pytestmark = pytest.mark.gpu
+
+W = np.array([4 / 9] + [1 / 9] * 4 + [1 / 36] * 4)
+CASES = [(70, 40, 300.0), (33, 65, 100.0), (64, 64, 200.0)]
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    from paper_2211_05009_amd import lbm as m
+    return m
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32s"])
+@pytest.mark.parametrize("variant", [0, 12, 16])
+@pytest.mark.parametrize("calls", [(100,), (300, 57, 43, 200), (250, 250), (1300, 100)])
+def test_calls_of_whole_chunks(lbm, dtype, variant, calls):
+    nx, ny, re = zip(*CASES)
+    b = lbm.Batch(nx, ny, re, u_lid=U_LID, dtype=dtype)
+    b.set_option(lbm.LBM_OPT_STEP_VARIANT, variant)
+    f0 = [W[:, None, None] + random_shift(x, y, k) for k, (x, y, _) in enumerate(CASES)]
+    for k, f in enumerate(f0):
+        b.set_populations(k, f)
+    for n in calls:
+        b.step(n)
+    for k, (x, y, r) in enumerate(CASES):
+        c = lbm.Cavity(x, y, re=r, u_lid=U_LID, dtype=dtype)
+        c.set_option(lbm.LBM_OPT_STEP_VARIANT, 0)
+        c.set_populations(f0[k])
+        c.step(sum(calls))
+        assert np.array_equal(b.get_populations(k), c.get_populations()), k
+        st = b.status(k)
+        assert (st["steps_done"], st["residual_step"]) == (c.steps_done, c.residual()[1])
+        assert abs(st["residual"] - c.residual()[0]) <= 1e-12 * c.residual()[0]
+        c.close()
+    b.close()
+
+
+def test_threshold_is_checked_at_every_monitor(lbm):
+    """A loose threshold drops each cavity at its first valid monitor, step
+    100, in a call of 500 steps."""
+    nx, ny, re = zip(*CASES)
+    b = lbm.Batch(nx, ny, re, u_lid=U_LID, dtype="f64")
+    for k, (x, y, _) in enumerate(CASES):
+        b.set_populations(k, W[:, None, None] + random_shift(x, y, k))
+    b.set_threshold(1e3)
+    b.step(500)
+    for k in range(len(CASES)):
+        st = b.status(k)
+        assert not st["active"] and st["steps_done"] == 100
+    b.close()
