@@ -61,7 +61,7 @@ struct lbm_batch {
   std::vector<double> last_res, last_mass;
   int64_t t_global = 0;
   double threshold = 0.0;
-  int variant = 12, use_graph = 1, graph_steps = 1000;   // 12: K = 5 on 32 x 32 tiles
+  int variant = 12, use_graph = 1, graph_steps = 1000;   // variant: default_shape
   hipStream_t stream = nullptr, own_stream = nullptr, cap_stream = nullptr;
   hipGraphExec_t graph = nullptr;       // graph_steps steps
   hipGraphExec_t graph1 = nullptr;      // one 100-step chunk, for calls that do not fill those
@@ -92,10 +92,27 @@ const Shape kShapes[] = {
     {0, 8, 2, 1, 0, 0, 0, 0},   {0, 16, 1, 1, 0, 0, 0, 0},  {1, 1, 1, 1, 0, 0, 0, 0},
     {1, 2, 1, 1, 0, 0, 0, 0},   {1, 4, 1, 1, 0, 0, 0, 0},   {1, 8, 1, 1, 0, 0, 0, 0},
     {2, 0, 0, 5, 32, 32, 32, 32}, {2, 0, 0, 5, 64, 16, 64, 16}, {2, 0, 0, 5, 16, 16, 16, 16},
-    {2, 0, 0, 10, 32, 32, 32, 16}, {2, 0, 0, 2, 32, 32, 32, 32}, {2, 0, 0, 5, 64, 32, 64, 16}};
-const int kNumShapes = 18;
+    {2, 0, 0, 10, 32, 32, 32, 16}, {2, 0, 0, 2, 32, 32, 32, 32}, {2, 0, 0, 5, 64, 32, 64, 16},
+    {2, 0, 0, 5, 32, 16, 32, 16}, {2, 0, 0, 5, 32, 16, 32, 16}};
+const int kNumShapes = 20;
 
 int shape_steps(int v) { return kShapes[v].k; }
+
+// The shape a new batch starts with (lbm_batch_autotune refines it), by its
+// total sites; K = 5 in all.  us per step on one MI355X, shape 12 (32 x 32,
+// 1024 threads) / 18 (32 x 16, 960) / 19 (32 x 16, 512):
+//   FP64: 4 x 500 wide (0.4 M sites) 5.1 / 4.5 / 4.7, 25 x 200 (1.2 M) 14.7 / 11.6 /
+//     11.6, 12 x 350 (1.5 M) 15.3 / 13.3 / 13.1, 25 x 500 (7.5 M) 76.5 / 65.0 / 61.4;
+//   FP32: 4 x 64 1.37 / 1.18 / 1.32, 4 x 150 (36 k) 1.61 / 1.23 / 1.36, 25 x 64
+//     (122 k) 1.79 / 1.74 / 1.84, 25 x 150 (0.7 M) 4.24 / 4.56 / 4.38, 25 x 500 33.2 /
+//     39.3 / 33.0.
+// An FP64 32 x 32 region leaves one block per CU; with 32 x 16 tiles two
+// fit, and from about 1.3 M sites the smaller blocks hide more of each other's
+// waits.  FP32 takes the small tile only while the batch leaves CUs idle.
+int default_shape(long long sites, int dtype) {
+  if (dtype == LBM_F64) return sites < 1300000 ? 18 : 19;
+  return sites < 130000 ? 18 : 12;
+}
 
 template <typename T, bool S, int BY, int RY>
 hipError_t launch_b(const lbm_batch *b, const void *src, void *dst, hipStream_t st) {
@@ -134,7 +151,7 @@ hipError_t launch_bt(const lbm_batch *b, const void *src, void *dst, hipStream_t
   return hipGetLastError();
 }
 
-// mon applies to the multi-step shapes (12-17) only.
+// mon applies to the multi-step shapes (12 on) only.
 template <typename T, bool S>
 hipError_t launch_b_variant(const lbm_batch *b, const void *src, void *dst, hipStream_t st,
                             int mon) {
@@ -150,6 +167,8 @@ hipError_t launch_b_variant(const lbm_batch *b, const void *src, void *dst, hipS
     case 17:
       if constexpr (D) return launch_bt<T, S, 5, 64, 16, 1024>(b, src, dst, st, mon);
       else return launch_bt<T, S, 5, 64, 32, 1024>(b, src, dst, st, mon);
+    case 18: return launch_bt<T, S, 5, 32, 16, 960>(b, src, dst, st, mon);
+    case 19: return launch_bt<T, S, 5, 32, 16, 512>(b, src, dst, st, mon);
     case 8: return launch_bv<T, S, 1>(b, src, dst, st);
     case 9: return launch_bv<T, S, 2>(b, src, dst, st);
     case 10: return launch_bv<T, S, 4>(b, src, dst, st);
@@ -529,6 +548,7 @@ int lbm_batch_create(int n, const int *nx, const int *ny, const double *re, doub
   if (elems >= (1LL << 31) || sites >= (1LL << 31))
     return bail(lbm_fail(LBM_EINVAL, "batch too large for 32-bit element offsets"));
   b->elems = (size_t)elems;
+  b->variant = default_shape(sites, dtype);
   const size_t esz = dtype == LBM_F64 ? 8 : 4;
   b->buf_bytes = b->elems * esz;
   b->active.assign(n, 1);

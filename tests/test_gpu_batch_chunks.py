@@ -22,7 +22,7 @@ def lbm():
 
 
 @pytest.mark.parametrize("dtype", ["f64", "f32s"])
-@pytest.mark.parametrize("variant", [0, 12, 16])
+@pytest.mark.parametrize("variant", [0, 12, 16, 18, 19])
 @pytest.mark.parametrize("calls", [(100,), (300, 57, 43, 200), (250, 250), (1300, 100)])
 def test_calls_of_whole_chunks(lbm, dtype, variant, calls):
     nx, ny, re = zip(*CASES)
@@ -59,3 +59,23 @@ def test_threshold_is_checked_at_every_monitor(lbm):
         st = b.status(k)
         assert not st["active"] and st["steps_done"] == 100
     b.close()
+
+
+@pytest.mark.parametrize("dtype,side,n,shape", [
+    ("f32s", 100, 12, 18), ("f32s", 100, 13, 12),      # 130,000 sites
+    ("f64", 500, 5, 18), ("f64", 512, 5, 19),          # 1.3 M sites
+])
+def test_default_shape(lbm, dtype, side, n, shape):
+    b = lbm.Batch([side] * n, [side] * n, [2.0 * side] * n, u_lid=U_LID, dtype=dtype)
+    assert b.get_option(lbm.LBM_OPT_STEP_VARIANT) == shape
+    f = W[:, None, None] + random_shift(side, side, 3)
+    b.set_populations(n - 1, f)
+    b.step(200)
+    c = lbm.Cavity(side, side, re=2.0 * side, u_lid=U_LID, dtype=dtype)
+    c.set_option(lbm.LBM_OPT_STEP_VARIANT, 0)
+    c.set_populations(f)
+    c.step(200)
+    assert np.array_equal(b.get_populations(n - 1), c.get_populations())
+    assert abs(b.residuals()[n - 1] - c.residual()[0]) <= 1e-12 * c.residual()[0]
+    b.close()
+    c.close()
