@@ -112,24 +112,21 @@ void conv_mn(const ConvArgs &a, int M, int N, hipStream_t st) {
   hipLaunchKernelGGL((k_conv_mn<MODE, WM, WN, TM, TN>), grid, dim3(256), 0, st, a);
 }
 
-// Tile shape for an M x N product: N tiles as wide as the channel count
-// allows (no MFMA on padding), and the larger M tile while it still gives
-// at least two blocks per CU.
-// Persistent patch-kernel blocks: two per CU (their LDS and registers allow
-// two), each walking its share of the tiles.
-constexpr int kPatchBlocks = 2 * 256;
-
-template <int MODE, int W, int BN>
-void conv_patch(const ConvArgs &a, int M, int N, hipStream_t st) {
-  constexpr int TPIX = W == 128 ? 256 : W == 16 ? 64 : 128;   // as in k_conv_patch
-  const int ntiles = M / TPIX * ((N + BN - 1) / BN);
-  const int grid = std::min(ntiles, kPatchBlocks);
-  hipLaunchKernelGGL((k_conv_patch<MODE, W, BN>), dim3(grid), dim3(256), 0, st, a, ntiles);
+// One forward or input-gradient pass by k_conv_tile.
+template <int MODE, int RT, int WR, int WC>
+void conv_tile(const ConvArgs &a, hipStream_t st) {
+  const int ntx = a.w / (16 * WC), nty = (a.h + RT * WR - 1) / (RT * WR);
+  const dim3 grid(a.n * ntx * nty * ((MODE == FWD ? a.co : a.ci) / 32));
+  if ((MODE == FWD ? a.ci : a.co) == 32)
+    hipLaunchKernelGGL((k_conv_tile<MODE, RT, WR, WC, true>), grid, dim3(256), 0, st, a, ntx, nty);
+  else
+    hipLaunchKernelGGL((k_conv_tile<MODE, RT, WR, WC, false>), grid, dim3(256), 0, st, a, ntx,
+                       nty);
 }
 
-// Whether conv_fd takes the patch kernel for a w x h image: whole-row tiles
-// (2 rows at widths 128 and 64, 4 at 32 and 16) and 16-byte output vectors.
-inline bool patch_path(int w, int h, int os, int oo) {
+// Whether conv_fd takes k_conv_tile for a w x h image: widths of whole tiles,
+// heights that the pairs of rows fit, 16-byte output vectors.
+inline bool tile_path(int w, int h, int os, int oo) {
   if (os % 8 || oo % 8) return false;
   return ((w == 128 || w == 64) && h % 2 == 0) || ((w == 32 || w == 16) && h % 4 == 0);
 }
@@ -137,31 +134,25 @@ inline bool patch_path(int w, int h, int os, int oo) {
 template <int MODE>
 void conv_fd(const ConvArgs &a, hipStream_t st) {
   const int M = a.n * a.h * a.w, N = MODE == FWD ? a.co : a.ci;
-  // direct convolution from an LDS patch of whole rows: 256-pixel tiles of
-  // 32 channels on 128-wide images, 128-pixel tiles on 64- and 32-wide
-  // ones, 64-pixel tiles on 16-wide ones (64 channels where N allows)
-  // (the forward patch kernel reads the transposed weight copy a.wtt)
-  const bool out_ok = patch_path(a.w, a.h, a.os, a.oo) && (MODE != FWD || a.wtt);
-  const bool n64 = N % 64 == 0;
-  if (out_ok && a.w == 128 && a.h % 2 == 0) {
-    conv_patch<MODE, 128, 32>(a, M, N, st);
+  // The kernel reads an image through a 2 GB buffer and, forward, the packed
+  // weights.  8 x 32-pixel tiles reuse weights and halo rows most, so they
+  // are taken where they give more than one block per CU; with fewer, 4 x 32
+  // (4 rows per wave, twice the blocks) hide more: 64 > 128 channels at
+  // 32 x 64, batch 8: 6.25 against 6.7 us, its input gradient 6.4 against
+  // 8.5 us; at 512 blocks (64 > 64 at 64 x 128) 13.4 against 11.7 us.
+  if (tile_path(a.w, a.h, a.os, a.oo) && (MODE != FWD || a.wf) &&
+      (long long)a.h * a.w * a.xs * 2 < 0x7f000000LL) {
+    if (a.w == 16)
+      conv_tile<MODE, 4, 2, 1>(a, st);
+    else if ((long long)a.n * ((a.h + 7) / 8) * (a.w / 32) * (N / 32) > 256)
+      conv_tile<MODE, 8, 1, 2>(a, st);
+    else
+      conv_tile<MODE, 4, 1, 2>(a, st);
     return;
   }
-  if (out_ok && a.w == 64 && a.h % 2 == 0) {
-    if (n64) conv_patch<MODE, 64, 64>(a, M, N, st);
-    else conv_patch<MODE, 64, 32>(a, M, N, st);
-    return;
-  }
-  if (out_ok && a.w == 32 && a.h % 4 == 0) {
-    if (n64) conv_patch<MODE, 32, 64>(a, M, N, st);
-    else conv_patch<MODE, 32, 32>(a, M, N, st);
-    return;
-  }
-  if (out_ok && a.w == 16 && a.h % 4 == 0) {
-    if (n64) conv_patch<MODE, 16, 64>(a, M, N, st);
-    else conv_patch<MODE, 16, 32>(a, M, N, st);
-    return;
-  }
+  // Tile shape of the GEMM: N tiles as wide as the channel count allows (no
+  // MFMA on padding), and the larger M tile while it still gives at least
+  // two blocks per CU.
   const long long big = 512;
   if (N % 128 == 0) {
     if ((long long)((M + 127) / 128) * (N / 128) >= big)
@@ -314,7 +305,8 @@ struct lbm_surrogate {
   uint16_t *act = nullptr, *gact = nullptr;     // activations and their gradients
   float *w = nullptr, *m = nullptr, *v = nullptr, *gw = nullptr;   // FP32 params
   uint16_t *wb = nullptr;                        // bf16 copy of the params
-  uint16_t *wbt = nullptr;                       // bf16 conv weights as [9][co][ci]
+  uint16_t *wbf = nullptr, *wbd = nullptr;       // bf16 conv weights in fragment order
+                                                 // (forward, input gradient)
   ConvTable convs{};                             // offsets and shapes of the convs
   float *target = nullptr, *mask = nullptr, *out3 = nullptr;
   float *loss_dev = nullptr, *loss_host = nullptr;
@@ -498,7 +490,7 @@ int forward(lbm_surrogate *s, int n) {
       a.xs = o.in.cs;
       a.xo = o.in.co;
       a.wt = s->wb + o.woff;
-      a.wtt = s->wbt + o.woff;
+      a.wf = s->wbf + o.woff;
       a.bias = s->w + o.boff;
       a.relu = o.relu;
       a.out = bptr(s, s->act, o.out);
@@ -557,7 +549,7 @@ void plan_relu_masks(lbm_surrogate *s) {
 }
 
 // A pool or upsample op that reads exactly the output of the conv just
-// before it is done by that conv's forward epilogue (patch kernel only).
+// before it is done by that conv's forward epilogue (k_conv_tile only).
 void plan_fwd_fusion(lbm_surrogate *s) {
   const int nop = (int)s->ops.size();
   s->fwd_into.assign(nop, -1);
@@ -565,7 +557,7 @@ void plan_fwd_fusion(lbm_surrogate *s) {
   for (int p = 0; p + 1 < nop; ++p) {
     const Op &o = s->ops[p], &q = s->ops[p + 1];
     if (o.type != OP_CONV || q.type == OP_CONV) continue;
-    if (!patch_path(level_w(o.level), level_h(o.level), o.out.cs, o.out.co)) continue;
+    if (!tile_path(level_w(o.level), level_h(o.level), o.out.cs, o.out.co)) continue;
     if (q.in.buf != o.out.buf || q.in.cs != o.out.cs || q.in.co != o.out.co || q.ci != o.co)
       continue;
     // the pool writes a dense tensor of the conv's channels; the upsample
@@ -629,6 +621,7 @@ int backward(lbm_surrogate *s, int n) {
         d.xs = o.out.cs;
         d.xo = o.out.co;
         d.wt = s->wb + o.woff;
+        d.wf = s->wbd + o.woff;
         d.out = bptr(s, s->gact, o.in);
         d.os = o.in.cs;
         d.oo = o.in.co;
@@ -656,12 +649,12 @@ int backward(lbm_surrogate *s, int n) {
 
 const View &head_view(lbm_surrogate *s) { return s->ops.back().out; }
 
-// Refresh the transposed bf16 weights after the bf16 copy changed.
-hipError_t transpose_weights(lbm_surrogate *s) {
+// Refresh the packed bf16 weights after the bf16 copy changed.
+hipError_t pack_weights(lbm_surrogate *s) {
   long long total = 0;
   for (int k = 0; k < s->convs.count; ++k) total += 9LL * s->convs.ci[k] * s->convs.co[k];
-  hipLaunchKernelGGL(k_transpose_weights, dim3(blocks_for(total)), dim3(256), 0, s->stream,
-                     s->wb, s->wbt, s->convs, total);
+  hipLaunchKernelGGL(k_pack_weights, dim3(blocks_for(total / 8)), dim3(256), 0, s->stream, s->wb,
+                     s->wbf, s->wbd, s->convs, total);
   return hipGetLastError();
 }
 
@@ -727,21 +720,22 @@ int lbm_nn_conv3x3(int mode, int n, int h, int w, int ci, int co, const void *x,
     HIPC(conv_launch(mode, a, (hipStream_t)stream));
     return LBM_OK;
   }
-  if (mode == FWD) {   // the weights transposed in a workspace of this call
-    uint16_t *wtt = nullptr;
-    HIPC(hipMalloc(&wtt, sizeof(uint16_t) * 9 * (size_t)ci * co));
+  if (mode == FWD) {   // the weights packed in a workspace of this call
+    uint16_t *wf = nullptr;
+    HIPC(hipMalloc(&wf, sizeof(uint16_t) * 9 * (size_t)ci * co));
     ConvTable tb{};
     tb.count = 1;
     tb.ci[0] = ci;
     tb.co[0] = co;
     const long long total = 9LL * ci * co;
-    hipLaunchKernelGGL(k_transpose_weights, dim3(blocks_for(total)), dim3(256), 0,
-                       (hipStream_t)stream, (const uint16_t *)wt, wtt, tb, total);
-    a.wtt = wtt;
+    hipLaunchKernelGGL(k_pack_weights, dim3(blocks_for(total / 8)), dim3(256), 0,
+                       (hipStream_t)stream, (const uint16_t *)wt, wf, (uint16_t *)nullptr, tb,
+                       total);
+    a.wf = wf;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = conv_launch(mode, a, (hipStream_t)stream);
     if (e == hipSuccess) e = hipStreamSynchronize((hipStream_t)stream);
-    (void)hipFree(wtt);
+    (void)hipFree(wf);
     if (e != hipSuccess) return lbm_fail(LBM_EDEVICE, "%s", hipGetErrorString(e));
     return LBM_OK;
   }
@@ -811,7 +805,7 @@ int lbm_sur_destroy(lbm_sur_t s) {
   if (!s) return LBM_OK;
   if (s->stream) (void)hipStreamSynchronize(s->stream);
   if (s->side) (void)hipStreamSynchronize(s->side);
-  void *ptrs[] = {s->act, s->gact, s->w, s->m, s->v, s->gw, s->wb, s->wbt, s->target, s->mask,
+  void *ptrs[] = {s->act, s->gact, s->w, s->m, s->v, s->gw, s->wb, s->wbf, s->wbd, s->target, s->mask,
                   s->out3, s->loss_dev, s->rearr, s->field, s->part};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -875,8 +869,10 @@ int lbm_sur_create(int max_batch, lbm_sur_t *out) {
       part_floats = std::max(part_floats, wgrad_part_floats(max_batch, level_h(o.level),
                                                             level_w(o.level), o.ci, o.co));
   if (e == hipSuccess) e = hipMalloc(&s->part, part_floats * sizeof(float));
-  if (e == hipSuccess) e = hipMalloc(&s->wbt, s->nparams * 2);
-  if (e == hipSuccess) e = hipMemsetAsync(s->wbt, 0, s->nparams * 2, s->stream);
+  if (e == hipSuccess) e = hipMalloc(&s->wbf, s->nparams * 2);
+  if (e == hipSuccess) e = hipMalloc(&s->wbd, s->nparams * 2);
+  if (e == hipSuccess) e = hipMemsetAsync(s->wbf, 0, s->nparams * 2, s->stream);
+  if (e == hipSuccess) e = hipMemsetAsync(s->wbd, 0, s->nparams * 2, s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->act, 0, s->act_elems * 2, s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->gact, 0, s->act_elems * 2, s->stream);
   if (e == hipSuccess) e = hipMemsetAsync(s->w, 0, s->nparams * 4, s->stream);
@@ -915,7 +911,7 @@ int lbm_sur_set_params(lbm_sur_t s, const float *params_host, int64_t n) {
   hipLaunchKernelGGL(k_to_bf16, dim3(blocks_for((long long)s->nparams)), dim3(256), 0, s->stream,
                      s->w, s->wb, (long long)s->nparams);
   HIPC(hipGetLastError());
-  HIPC(transpose_weights(s));
+  HIPC(pack_weights(s));
   s->adam_t = 0;
   HIPC(hipStreamSynchronize(s->stream));
   return LBM_OK;
@@ -1002,7 +998,7 @@ int lbm_sur_train_step(lbm_sur_t s, int n, const double *re, const double *ar,
                        s->w, s->m, s->v, s->gw, s->wb, (long long)s->nparams, (float)lr, (float)b1,
                        (float)b2, 1e-8f, (float)c1, (float)c2);
     HIPC(hipGetLastError());
-    HIPC(transpose_weights(s));
+    HIPC(pack_weights(s));
   }
   HIPC(hipMemcpyAsync(s->loss_host, s->loss_dev, sizeof(float), hipMemcpyDeviceToHost, s->stream));
   HIPC(hipStreamSynchronize(s->stream));

@@ -11,8 +11,8 @@
 //   dgrad   : GX[p, c]     = sum_{t,o} GY[p - d_t, o] W[t, c, o]
 //   wgrad   : GW[t, c, o] += sum_p     X[p + d_t, c] GY[p, o]
 // all on v_mfma_f32_16x16x32_bf16 (FP32 accumulate): forward and dgrad as a
-// direct convolution from an LDS patch of whole image rows (k_conv_patch)
-// or, for widths it does not serve, a pipelined implicit GEMM (k_conv_mn);
+// direct convolution from an LDS patch (k_conv_tile) or, for widths it does
+// not serve, a pipelined implicit GEMM (k_conv_mn);
 // wgrad streamed over strips of image rows with all nine taps per block
 // (k_wgrad_rows: widths 16-128) or as a pipelined GEMM over pixel chunks
 // (k_wgrad: any width), the per-strip or per-chunk partials added in a
@@ -20,6 +20,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 namespace lbm {
 namespace nn {
@@ -46,7 +48,8 @@ struct ConvArgs {
   const uint16_t *g;   // WGRAD: output gradient
   int gs, go;
   const uint16_t *wt;  // FWD / DGRAD: bf16 weights [9][ci][co]
-  const uint16_t *wtt; // FWD (optional): the same weights as [9][co][ci]
+  const uint16_t *wf;  // FWD / DGRAD (optional): the same weights in this pass's
+                       // MFMA fragment order (k_pack_weights)
   const float *bias;   // FWD: per output channel (may be null)
   int relu;            // FWD: apply max(0, .)
   void *out;           // FWD: bf16 Y; DGRAD: bf16 GX; WGRAD: float GW [9 ci][co]
@@ -55,7 +58,7 @@ struct ConvArgs {
   const uint16_t *mask;  // DGRAD (optional): zero GX where mask <= 0 (the
                          // ReLU of the layer that produced the input; same
                          // stride and offset as out), before the bf16 rounding
-  // FWD, patch kernel (optional): the layer's output also goes, as the next
+  // FWD, k_conv_tile (optional): the layer's output also goes, as the next
   // op would write it, to
   uint16_t *pool_out;  // its 2 x 2 average pool, dense [n][h/2][w/2][co]
   uint16_t *up_out;    // its nearest 2x upsampling, a slice (ups, upo) of
@@ -223,277 +226,280 @@ __global__ __launch_bounds__(256) void k_conv_mn(ConvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// The same two passes as direct convolutions: a tile is TPIX = R w pixels
-// (R whole rows of one image; w a multiple of 16, R dividing h) by BN
-// output channels; per chunk of 32 input channels the block loads the
-// (R + 2) x (w + 2) patch of the input (zero halo) and the 9 taps' weights
-// into LDS once, and runs the 9 taps' MFMAs out of LDS, instead of gathering
-// a shifted copy of the input from global memory for every tap.  Four waves
-// split the TPIX pixels (TPIX / 64 MFMA row tiles each) and share all BN
-// columns.  The epilogue stages the FP32 tile in LDS (over patch and
-// weights) and writes whole 16-byte vectors of 8 channels.  Patch pixels
-// and FP32 rows are padded in LDS so that neither the MFMA operand reads
-// nor the epilogue's writes conflict on banks.
-// In the forward pass the epilogue can also write the output's 2 x 2 average
-// pool or its nearest 2x upsampling (ConvArgs pool_out, up_out), the next
-// op of the network, from the tile it holds.
-// The blocks are persistent: block b takes tiles b, b + G, b + 2 G, ... (G
-// blocks, numbered so that each XCD holds a contiguous range of tiles) and
-// walks their (tile, chunk) steps in order, loading the next step's patch
-// and weights into registers while the current step's MFMAs and, at a
-// tile's last chunk, its epilogue run; so memory and matrix cores stay busy
-// together instead of every block loading, then computing, then storing.
-//   FWD  : out[p][o] = sum_{t,c} X[p + d_t][c] W[t][c][o]   (N = co, chunks of ci)
-//   DGRAD: out[p][c] = sum_{t,o} GY[p - d_t][o] W[t][c][o]  (N = ci, chunks of co)
-// LDS elements per patch pixel: 32 channels + 8 pad, so the 16-byte reads of
-// 8 lanes at consecutive pixels (80-byte stride) cover all 32 banks once
-constexpr int kPs = 40;
+// The same two passes as direct convolutions, out[p][n] = sum over chunks of
+// 32 input channels, then over the 9 taps, of IN[p +- d_t][k] W[t][n][k]
+// (FWD: n = output channel, k = input channel; DGRAD the other way round and
+// the taps mirrored).  A block of four waves computes BR rows x BC columns of
+// one image by 32 channels, two waves along the pixels and two along the
+// channels; a wave holds RT rows x 16 columns x 16 channels as RT MFMA tiles
+// (channels x pixels: a lane's four results are four channels of one pixel).
+//
+// What bounds it: at the batch sizes of the network a layer has one or two
+// waves per SIMD, so what matters is that neither LDS nor the vector memory
+// path nor a barrier holds the MFMAs up.
+//  * Weights never enter LDS: a wave needs its own 9 fragments of a chunk,
+//    and reads the next chunk's from a copy laid out in fragment order (9
+//    loads of 1 KB each, pack_weights) while it works on this one's.
+//  * A patch row's fragment (16 pixels, shifted by dx) serves the up to three
+//    output rows it is a tap of: 3 (RT + 2) LDS reads for 9 RT MFMAs, in an
+//    order that still adds each output's taps 0 to 8 in turn.
+//  * The patch (halo included; pixels outside the image come back as zeros
+//    from buffer loads) lies in LDS with 64 bytes a pixel, the 16-byte groups
+//    of every second quad of columns swapped by twos: no two lanes of a read
+//    meet on a bank (4.3 clocks per wave read; 80 bytes a pixel took 8.0).
+//  * Two patch buffers, the stores of chunk c + 1 and the loads of c + 2 and of
+//    the weights spread between the MFMAs of chunk c: one barrier a chunk.
+//  * The epilogue works in registers; v_permlane16_swap pairs two rows so
+//    that every store is 16 bytes.
+// Layers with one chunk (ONE) have nothing to prefetch: a single buffer and
+// 100 registers instead of 211 let a CU hold five blocks instead of two.
+// Measured (batch 8, the network's 15 layers, against whole-row tiles with
+// patch and weights staged through LDS): forward 248 -> 182 us, input gradient
+// 270 -> 188 us; 384 > 128 channels at 32 x 64 29.0 -> 17.0 us (850 TFLOP/s),
+// 32 > 32 at 128 x 256 14.5 -> 10.5 us (3.2 TB/s, 6.7 us at a copy's rate).
 
-template <int MODE, int W, int BN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_patch(
-    ConvArgs a, int ntiles) {
-  // tile: R whole rows of W pixels, TPIX = R W (256 at W = 128, 128 at
-  // W = 64 and 32, 64 at W = 16)
-  constexpr int TPIX = W == 128 ? 256 : W == 16 ? 64 : 128;
-  constexpr int R = TPIX / W, PW = W + 2, PP = (R + 2) * PW;
-  constexpr int TM = TPIX / 64, TN = BN / 16;
-  constexpr int OS = BN + 4;   // padded FP32 row: the 4 lane groups' writes fill 2 bank cycles
-  // one LDS buffer: the patch [pixel][32 channels + pad] and the weights
-  // [tap][n][k] while the taps run, the FP32 tile [pixel][OS] in the epilogue
-  constexpr int PS_EL = PP * kPs, WS_EL = 9 * BN * kLdsK;
-  constexpr int SM_EL = PS_EL + WS_EL > TPIX * OS * 2 ? PS_EL + WS_EL : TPIX * OS * 2;
-  static_assert(TM >= 1 && SM_EL * 2 <= 80 * 1024, "two blocks per CU");
-  constexpr int PV = (PP * 4 + 255) / 256;            // patch vectors per thread
-  constexpr int WV = (9 * 32 * (BN / 8) + 255) / 256;  // weight vectors per thread
-  __shared__ __align__(16) uint16_t Sm[SM_EL];
-  uint16_t *const Ps = Sm, *const Ws = Sm + PS_EL;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int HW = a.h * W;
-  const int C = MODE == FWD ? a.ci : a.co;
-  const int N = MODE == FWD ? a.co : a.ci;
-  const int ntn = (N + BN - 1) / BN;   // column tiles per pixel tile (adjacent tile numbers)
+// the value of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ float lane_xor1(float v) {
+  return __uint_as_float(
+      __builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0xB1, 0xF, 0xF, true));
+}
 
-  // Tile being loaded: its first output channel, and the image pixels of
-  // this thread's patch vectors (-1: halo outside the image, or beyond the
-  // patch); a thread's vectors all hold channels pkq .. pkq + 7 of a chunk.
-  int ln0 = 0;
-  int ppix[PV];
+// v_permlane16_swap: [a0 a1 a2 a3], [b0 b1 b2 b3] (rows of 16 lanes) become
+// [a0 b0 a2 b2], [a1 b1 a3 b3]
+__device__ __forceinline__ void swap16(float &a, float &b) {
+  const auto r =
+      __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+template <int MODE, int RT, int WR, int WC, bool ONE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ONE ? 4 : 2))) void
+k_conv_tile(ConvArgs a, int ntx, int nty) {
+  static_assert(WR * WC == 2 && RT % 2 == 0, "two waves along the pixels");
+  constexpr int BR = RT * WR, BC = 16 * WC;
+  // patch rows of a multiple of 4 pixels, so that a row's columns have the
+  // same banks whatever the row
+  constexpr int PW = BC + 4, PP = (BR + 2) * PW;
+  constexpr int PV = (PP * 4 + 255) / 256;   // 16-byte patch vectors per thread
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) uint16_t Sm[ONE ? 1 : 2][PP * 32];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wr = WR == 2 ? wave >> 1 : 0, wc = WC == 2 ? wave >> 1 : 0;
+  const int C = MODE == FWD ? a.ci : a.co, N = MODE == FWD ? a.co : a.ci;
+  // block -> channels fastest, then tile column, tile row, image: the blocks
+  // of one XCD share patches and halos in its L2
+  const int ntn = N / 32, b = xcd_block(blockIdx.x, gridDim.x);
+  const int n0 = b % ntn * 32 + (wave & 1) * 16;   // this wave's first channel
+  const int pt = b / ntn, tx = pt % ntx, ty = pt / ntx % nty, img = pt / (ntx * nty);
+  const int y0 = ty * BR, x0 = tx * BC;
+  const int fr = lane & 15, g = lane >> 4;
+
+  // byte offsets in the image of this thread's patch vectors (out of the
+  // buffer's range where there is no pixel: such loads return zeros)
+  int poff[PV];
   const int pkq = (tid & 3) * 8;
-  auto set_load_tile = [&](int tile) {
-    const int lm0 = tile / ntn * TPIX;
-    ln0 = tile % ntn * BN;
-    const int img = lm0 / HW, y0 = (lm0 - img * HW) / W;   // first row of the tile
 #pragma unroll
-    for (int u = 0; u < PV; ++u) {
-      const int pp = (tid + 256 * u) >> 2;
-      const int py = pp / PW, px = pp - py * PW;
-      const int gy = y0 + py - 1, gx = px - 1;
-      ppix[u] = (pp < PP && gy >= 0 && gy < a.h && gx >= 0 && gx < W) ? img * HW + gy * W + gx
-                                                                        : -1;
-    }
+  for (int u = 0; u < PV; ++u) {
+    const int pp = (tid + 256 * u) >> 2, py = pp / PW, px = pp - py * PW;
+    const int gy = y0 + py - 1, gx = x0 + px - 1;
+    poff[u] = (pp < PP && px < BC + 2 && gy >= 0 && gy < a.h && gx >= 0 && gx < a.w)
+                  ? ((gy * a.w + gx) * a.xs + pkq) * 2
+                  : 0x7ffffff0;
+  }
+  const uint32_t xbytes = (uint32_t)(a.h * a.w * a.xs - a.xo) * 2;
+  auto image = [&](bool on) {   // the input image (empty: loads cost nothing)
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(a.x + (size_t)img * a.h * a.w * a.xs + a.xo),
+                                             0, on ? xbytes : 0, 0x00020000);
   };
-
-  // One chunk of 32 channels: all its loads are issued into registers
-  // first (unrolled, so they are in flight together), then stored to LDS.
-  uint4 rp[PV], rw[WV];
-  auto load = [&](int c0) {
-    const int n0 = ln0;
+  // weight fragments: lane's 8 k of channel fr, k = 8 g; from the packed copy
+  // [n / 16][chunk][tap][lane][8], or straight from the rows [tap][n][k]
+  const uint16_t *wsrc;
+  int wlane, wtap, wchunk;
+  if (a.wf) {
+    wsrc = a.wf + (size_t)n0 * C * 9;
+    wlane = lane * 8;
+    wtap = 512;
+    wchunk = 9 * 512;
+  } else {   // DGRAD
+    wsrc = a.wt + (size_t)n0 * C;
+    wlane = fr * C + g * 8;
+    wtap = N * C;
+    wchunk = 32;
+  }
+  float bv[4] = {0.f, 0.f, 0.f, 0.f};
+  if (MODE == FWD && a.bias) {
 #pragma unroll
-    for (int u = 0; u < PV; ++u) {   // halo vectors read pixel 0 and are zeroed
-      const uint4 x = *(const uint4 *)(a.x + (size_t)(ppix[u] >= 0 ? ppix[u] : 0) * a.xs + a.xo +
-                                       pkq + c0);
-      rp[u] = ppix[u] >= 0 ? x : make_uint4(0, 0, 0, 0);
-    }
-    // weights as [tap][n][k] rows: FWD from the transposed copy WT[t][co][ci]
-    // (required), DGRAD from W[t][ci][co]; rows beyond the taps or N read row
-    // 0 and are zeroed, so every load is issued without a branch
-    const uint16_t *wsrc = MODE == FWD ? a.wtt : a.wt;
-#pragma unroll
-    for (int u = 0; u < WV; ++u) {
-      const int v = tid + 256 * u;
-      const int t = v / (BN * 4), r = v - t * BN * 4;
-      const int n = r >> 2, kq = (r & 3) * 8;
-      const bool ok = t < 9 && n0 + n < N;
-      const uint4 w = *(const uint4 *)(wsrc + ((size_t)(ok ? t * N + n0 + n : 0)) * C + c0 + kq);
-      rw[u] = ok ? w : make_uint4(0, 0, 0, 0);
-    }
-  };
-  auto stage = [&]() {
-#pragma unroll
-    for (int u = 0; u < PV; ++u) {
-      const int v = tid + 256 * u;
-      if ((v >> 2) < PP) *(uint4 *)&Ps[(v >> 2) * kPs + (v & 3) * 8] = rp[u];
-    }
-#pragma unroll
-    for (int u = 0; u < WV; ++u) {
-      const int v = tid + 256 * u;
-      const int t = v / (BN * 4), r = v - t * BN * 4;
-      if (t < 9) *(uint4 *)&Ws[(t * BN + (r >> 2)) * kLdsK + (r & 3) * 8] = rw[u];
-    }
-  };
-
-  floatx4 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-  const int fr = lane & 15, fk = (lane >> 4) * 8;
-  // LDS element offset of this lane's A fragment in each row tile at tap
-  // (1, 1) (the pixel itself)
-  int aoff[TM];
-#pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    const int q = wave * (TPIX / 4) + i * 16 + fr;
-    aoff[i] = ((q / W + 1) * PW + q % W + 1) * kPs + fk;
+    for (int e = 0; e < 4; ++e) bv[e] = a.bias[n0 + 4 * g + e];
   }
 
-  // epilogue of the tile at (m0, n0): lane holds rows 4 (lane / 16) + e,
-  // column lane % 16 of each MFMA tile; the FP32 tile goes to LDS
-  // [TPIX][OS], then each thread writes 8 consecutive channels of a pixel
-  auto epilogue = [&](int m0, int n0) {
-    float *Os = reinterpret_cast<float *>(Sm);
+  floatx4 acc[RT];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int r = 0; r < RT; ++r) acc[r] = floatx4{0.f, 0.f, 0.f, 0.f};
+  // LDS element of this lane's fragment in patch row 0, per tap column
+  int abase[3];
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
+  for (int dx = 0; dx < 3; ++dx) {
+    const int px = wc * 16 + fr + (MODE == FWD ? dx : 2 - dx);
+    abase[dx] = (wr * RT * PW + px) * 32 + ((g * 8) ^ ((px & 4) << 2));
+  }
+  u32x4 rp[PV];
+  auto put = [&](int bf, int u) {
+    const int pp = (tid + 256 * u) >> 2, px = pp % PW;
+    if (pp < PP) *(u32x4 *)&Sm[bf][pp * 32 + (pkq ^ ((px & 4) << 2))] = rp[u];
+  };
+  bf16x8 w0[9], w1[9];
+  {
+    const auto rs = image(true);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          Os[(wave * (TPIX / 4) + i * 16 + (lane >> 4) * 4 + e) * OS + j * 16 + (lane & 15)] =
-              acc[i][j][e];
-    // a thread always writes channels nq .. nq + 7 (256 is a multiple of
-    // BN / 8): their bias values are loaded once, all in flight together
-    const int nq = (tid % (BN / 8)) * 8;
-    float bv[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (MODE == FWD && a.bias && n0 + nq < N) {
+    for (int u = 0; u < PV; ++u) rp[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, poff[u], 0, 0);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) bv[j] = a.bias[n0 + nq + j];
+    for (int t = 0; t < 9; ++t) w0[t] = *(const bf16x8 *)(wsrc + t * (size_t)wtap + wlane);
+#pragma unroll
+    for (int u = 0; u < PV; ++u) put(0, u);
+    if (!ONE) {
+#pragma unroll
+      for (int u = 0; u < PV; ++u)
+        rp[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, poff[u], 64, 0);
     }
+  }
+
+  // One chunk (channels c0 .. c0 + 31) out of buffer bf with weights w; with
+  // chunks to come, also the next one's patch into the other buffer, its
+  // weights into wn and the loads of the patch after it.
+  auto chunk = [&](auto last_t, int bf, int c0, bf16x8(&w)[9], bf16x8(&wn)[9]) {
+    constexpr bool LAST = decltype(last_t)::value;
     __syncthreads();
-    if (n0 + nq >= N) return;
-    for (int v = tid; v < TPIX * (BN / 8); v += 256) {
-      const int pl = v / (BN / 8);
-      const float *src = Os + pl * OS + nq;
-      uint16_t *o = (uint16_t *)a.out + (size_t)(m0 + pl) * a.os + a.oo + n0 + nq;
-      float r[8];
+    const uint16_t *P = Sm[bf];
+    const auto rs = image(c0 + 64 < C);
+    const uint16_t *wp = wsrc + (size_t)(c0 / 32 + 1) * wchunk + wlane;
+    bf16x8 fa[2][3];
+    auto read_row = [&](int i) {
+      const int row = MODE == FWD ? i : RT + 1 - i;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) r[j] = src[j];
-      if (MODE == FWD) {
+      for (int dx = 0; dx < 3; ++dx)
+        fa[i & 1][dx] = *(const bf16x8 *)(P + abase[dx] + row * PW * 32);
+    };
+    read_row(0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          r[j] += bv[j];
-          if (a.relu) r[j] = fmaxf(r[j], 0.f);
+    for (int i = 0; i < RT + 2; ++i) {
+      if (i + 1 < RT + 2) read_row(i + 1);
+      if (!LAST) {
+        constexpr int WI = (9 + RT + 1) / (RT + 2), S0 = PV < RT + 2 ? (RT + 2 - PV) / 2 : 0;
+        static_assert(PV <= RT + 2, "one patch vector per row step");
+#pragma unroll
+        for (int q = 0; q < WI; ++q)
+          if (i * WI + q < 9)
+            wn[i * WI + q] = *(const bf16x8 *)(wp + (size_t)(i * WI + q) * wtap);
+        if (i >= S0 && i - S0 < PV) {
+          put(bf ^ 1, i - S0);
+          rp[i - S0] =
+              __builtin_amdgcn_raw_buffer_load_b128(rs, poff[i - S0], (c0 + 64) * 2, 0);
         }
-      } else {
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy) {
+          const int q = i - dy;
+          if (q < 0 || q >= RT) continue;
+          const int r = MODE == FWD ? q : RT - 1 - q;
+          acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[dy * 3 + dx], fa[i & 1][dx], acc[r],
+                                                           0, 0, 0);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  for (int c0 = 0;; c0 += 64) {
+    if (ONE || c0 + 32 >= C) {
+      chunk(std::true_type{}, 0, c0, w0, w1);
+      break;
+    }
+    chunk(std::false_type{}, 0, c0, w0, w1);
+    if (c0 + 64 >= C) {
+      chunk(std::true_type{}, 1, c0 + 32, w1, w0);
+      break;
+    }
+    chunk(std::false_type{}, 1, c0 + 32, w1, w0);
+  }
+
+  // Epilogue, rows in pairs: after the swap the lanes of even groups of 16
+  // hold 8 channels of row r, those of odd groups the same channels of r + 1.
+  const int x = x0 + wc * 16 + fr, yb = y0 + wr * RT, ch = n0 + 8 * (g >> 1);
+#pragma unroll
+  for (int r = 0; r < RT; r += 2) {
+    if (yb + r >= a.h) break;
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      v[e] = acc[r][e];
+      v[4 + e] = acc[r + 1][e];
+      if (MODE == FWD) {
+        v[e] += bv[e];
+        v[4 + e] += bv[e];
+        if (a.relu) {
+          v[e] = fmaxf(v[e], 0.f);
+          v[4 + e] = fmaxf(v[4 + e], 0.f);
+        }
+      }
+      swap16(v[e], v[4 + e]);
+    }
+    const int y = yb + r + (g & 1);
+    if (y < a.h) {
+      uint16_t *o = (uint16_t *)a.out + ((size_t)(img * a.h + y) * a.w + x) * a.os + a.oo + ch;
+      if (MODE == DGRAD) {
         if (a.accumulate) {
           const uint4 old = *(const uint4 *)o;
           const uint16_t *ov = (const uint16_t *)&old;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) r[j] += bf2f(ov[j]);
+          for (int e = 0; e < 8; ++e) v[e] += bf2f(ov[e]);
         }
         if (a.mask) {
           const uint4 mv = *(const uint4 *)(a.mask + (o - (uint16_t *)a.out));
           const uint16_t *mk = (const uint16_t *)&mv;
 #pragma unroll
-          for (int j = 0; j < 8; ++j)
-            if (!(bf2f(mk[j]) > 0.f)) r[j] = 0.f;
+          for (int e = 0; e < 8; ++e)
+            if (!(bf2f(mk[e]) > 0.f)) v[e] = 0.f;
         }
       }
       uint4 pk;
       uint16_t *pv = (uint16_t *)&pk;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pv[j] = f2bf(r[j]);
+      for (int e = 0; e < 8; ++e) pv[e] = f2bf(v[e]);
       *(uint4 *)o = pk;
       if (MODE == FWD && a.up_out) {   // the 2 x 2 copies at twice the resolution
-        const int p = m0 + pl, img = p / HW, y = (p - img * HW) / W, x = p % W;
-        uint16_t *u = a.up_out + ((size_t)(img * 2 * a.h + 2 * y) * (2 * W) + 2 * x) * a.ups +
-                      a.upo + n0 + nq;
+        uint16_t *u = a.up_out +
+                      ((size_t)(img * 2 * a.h + 2 * y) * (2 * a.w) + 2 * x) * a.ups + a.upo + ch;
         *(uint4 *)u = pk;
         *(uint4 *)(u + a.ups) = pk;
-        *(uint4 *)(u + (size_t)2 * W * a.ups) = pk;
-        *(uint4 *)(u + (size_t)(2 * W + 1) * a.ups) = pk;
+        *(uint4 *)(u + (size_t)2 * a.w * a.ups) = pk;
+        *(uint4 *)(u + (size_t)(2 * a.w + 1) * a.ups) = pk;
       }
     }
-    if (MODE == FWD && a.pool_out) {   // 2 x 2 means of the rounded outputs, in
-      // k_pool_fwd's order; the tile's R rows (R even) start at an even row
-      const int img = m0 / HW, y0 = (m0 - img * HW) / W;
-      for (int v = tid; v < TPIX / 4 * (BN / 8); v += 256) {
-        const int pp = v / (BN / 8), oy = pp / (W / 2), ox = pp % (W / 2);
-        float sm[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // 2 x 2 means of the rounded outputs, in k_pool_fwd's order (the image's
+    // height is even where there is a pool: the pair is whole)
+    if (MODE == FWD && a.pool_out) {
+      uint4 pk;
+      uint16_t *pv = (uint16_t *)&pk;
 #pragma unroll
-        for (int dy = 0; dy < 2; ++dy)
-#pragma unroll
-          for (int dx = 0; dx < 2; ++dx) {
-            const float *src = Os + ((2 * oy + dy) * W + 2 * ox + dx) * OS + nq;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              float r = src[j] + bv[j];
-              if (a.relu) r = fmaxf(r, 0.f);
-              sm[j] += bf2f(f2bf(r));
-            }
-          }
-        uint4 pk;
-        uint16_t *pv = (uint16_t *)&pk;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) pv[j] = f2bf(0.25f * sm[j]);
+      for (int e = 0; e < 8; ++e) {
+        float p00 = bf2f(f2bf(v[e])), p01 = lane_xor1(p00), p10 = p00, p11 = p01;
+        swap16(p00, p10);   // row r and row r + 1 in every lane
+        swap16(p01, p11);
+        float sm = 0.f;
+        sm += p00;
+        sm += p01;
+        sm += p10;
+        sm += p11;
+        pv[e] = f2bf(0.25f * sm);
+      }
+      if ((lane & 17) == 0)   // even columns, even groups
         *(uint4 *)(a.pool_out +
-                   ((size_t)(img * (a.h / 2) + y0 / 2 + oy) * (W / 2) + ox) * a.co + n0 + nq) = pk;
-      }
+                   ((size_t)(img * (a.h / 2) + (yb + r) / 2) * (a.w / 2) + x / 2) * a.co + ch) = pk;
     }
-  };
-
-  int tile = xcd_block(blockIdx.x, gridDim.x);   // gridDim.x <= ntiles
-  int c0 = 0;
-  set_load_tile(tile);
-  int em0 = tile / ntn * TPIX, en0 = ln0;        // tile whose sums acc holds
-  load(0);
-  stage();
-  __syncthreads();
-  for (;;) {
-    // the step after (tile, c0)
-    int ntile = tile, nc0 = c0 + 32;
-    if (nc0 >= C) {
-      ntile = tile + gridDim.x;
-      nc0 = 0;
-    }
-    const bool more = ntile < ntiles;
-    if (more) {   // in flight during this step's taps and epilogue
-      if (ntile != tile) set_load_tile(ntile);
-      load(nc0);
-    }
-#pragma unroll 3
-    for (int t = 0; t < 9; ++t) {
-      const int dy = t / 3, dx = t % 3;
-      // FWD reads pixel p + d_t, DGRAD p - d_t
-      const int oy = MODE == FWD ? dy - 1 : 1 - dy, ox = MODE == FWD ? dx - 1 : 1 - dx;
-      bf16x8 fa[TM], fb[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) fa[i] = *(const bf16x8 *)&Ps[aoff[i] + (oy * PW + ox) * kPs];
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        fb[j] = *(const bf16x8 *)&Ws[(t * BN + j * 16 + fr) * kLdsK + fk];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-    }
-    __syncthreads();   // patch and weights read by every wave
-    if (nc0 == 0) {    // the tile's last chunk: write it out
-      epilogue(em0, en0);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-      em0 = ntile / ntn * TPIX;
-      en0 = ntile % ntn * BN;
-      __syncthreads();   // the FP32 tile read by every thread
-    }
-    if (!more) break;
-    stage();
-    __syncthreads();
-    tile = ntile;
-    c0 = nc0;
   }
 }
 
@@ -872,19 +878,21 @@ __global__ __launch_bounds__(256 * KW) void k_wgrad_rows(ConvArgs a, int rows, f
   }
 }
 
-// Transposed bf16 weight copies WT[t][o][c] = W[t][c][o] of up to 16
-// convolutions at once (the parameter layout of the surrogate: conv k's
-// weights at element off[k]).
+// Weight copies in k_conv_tile's fragment order, [n / 16][chunk of 32 k][tap]
+// [lane][8] with lane = n % 16 + 16 (k % 32 / 8), of up to 16 convolutions at
+// once (the parameter layout of the surrogate: conv k's weights at element
+// off[k]): into wf for the forward pass (n = output, k = input channel) and
+// wd for the input gradient (the other way round); either may be null.  One
+// thread per lane vector.
 struct ConvTable {
   int count;
   long long off[16];
   int ci[16], co[16];
 };
-__global__ void k_transpose_weights(const uint16_t *w, uint16_t *wt, ConvTable tb,
-                                    long long total) {
-  const long long g = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  if (g >= total) return;
-  long long i = g;
+__global__ void k_pack_weights(const uint16_t *w, uint16_t *wf, uint16_t *wd, ConvTable tb,
+                               long long total) {
+  long long i = (blockIdx.x * (long long)blockDim.x + threadIdx.x) * 8;
+  if (i >= total) return;
   int k = 0;
   while (k < tb.count && i >= 9LL * tb.ci[k] * tb.co[k]) {
     i -= 9LL * tb.ci[k] * tb.co[k];
@@ -892,10 +900,22 @@ __global__ void k_transpose_weights(const uint16_t *w, uint16_t *wt, ConvTable t
   }
   if (k >= tb.count) return;
   const int ci = tb.ci[k], co = tb.co[k];
-  const int c = i % ci;
-  const long long r = i / ci;
-  const int o = r % co, t = r / co;
-  wt[tb.off[k] + i] = w[tb.off[k] + ((long long)t * ci + c) * co + o];
+  const uint16_t *src = w + tb.off[k];
+  const int lane = (int)(i >> 3) & 63, q = (int)(i >> 9), t = q % 9;
+#pragma unroll
+  for (int pass = 0; pass < 2; ++pass) {
+    uint16_t *dst = pass == 0 ? wf : wd;
+    if (!dst) continue;
+    const int nc = (pass == 0 ? ci : co) / 32;
+    const int n = q / 9 / nc * 16 + (lane & 15), k0 = q / 9 % nc * 32 + (lane >> 4) * 8;
+    uint4 v;
+    uint16_t *e = (uint16_t *)&v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      e[j] = pass == 0 ? src[((long long)t * ci + k0 + j) * co + n]
+                       : src[((long long)t * ci + n) * co + k0 + j];
+    *(uint4 *)(dst + tb.off[k] + i) = v;
+  }
 }
 
 // out[i] += sum over k of part[k][i] for i < n: the deterministic second half
