@@ -865,6 +865,7 @@ int lbm_destroy(lbm_t h) {
   if (h->aux_dev) (void)hipFree(h->aux_dev);
   if (h->mon_host) (void)hipHostFree(h->mon_host);
   if (h->vortex_host) (void)hipHostFree(h->vortex_host);
+  h->stage.release();
   if (h->tmp) (void)hipFree(h->tmp);
   if (h->probe_xy) (void)hipFree(h->probe_xy);
   if (h->probe_ring) (void)hipFree(h->probe_ring);
@@ -1220,12 +1221,9 @@ int lbm_moments(lbm_t h, double *rho, double *ux, double *uy) {
   if (h->dtype == LBM_F64) launch_moments_t<double, false>(h, d[0], d[1], d[2]);
   else launch_moments_t<float, true>(h, d[0], d[1], d[2]);
   HIPC(hipGetLastError());
-  double *outs[3] = {rho, ux, uy};
-  for (int k = 0; k < 3; ++k)
-    if (outs[k])
-      HIPC(hipMemcpyAsync(outs[k], d[k], n * sizeof(double), hipMemcpyDeviceToHost,
-                          h->stream));
-  HIPC(hipStreamSynchronize(h->stream));
+  const CopyOut outs[3] = {
+      {rho, d[0], n * sizeof(double)}, {ux, d[1], n * sizeof(double)}, {uy, d[2], n * sizeof(double)}};
+  HIPC(h->stage.copy(outs, 3, h->stream));
   return LBM_OK;
 }
 
@@ -1377,8 +1375,8 @@ int lbm_stream_function(lbm_t h, double *psi) {
   if (rc) return rc;
   rc = launch_psi(h, h->tmp);
   if (rc) return rc;
-  HIPC(hipMemcpyAsync(psi, h->tmp, n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPC(hipStreamSynchronize(h->stream));
+  const CopyOut out{psi, h->tmp, n * sizeof(double)};
+  HIPC(h->stage.copy(&out, 1, h->stream));
   return LBM_OK;
 }
 
@@ -1558,8 +1556,8 @@ int lbm_get_populations(lbm_t h, double *f) {
     hipLaunchKernelGGL((k_get_pop<float, true>), dim3((n + 255) / 256), dim3(256), 0,
                        h->stream, (const float *)h->buf[h->cur], geom(h), h->tmp);
   HIPC(hipGetLastError());
-  HIPC(hipMemcpyAsync(f, h->tmp, 9 * n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPC(hipStreamSynchronize(h->stream));
+  const CopyOut out{f, h->tmp, 9 * n * sizeof(double)};
+  HIPC(h->stage.copy(&out, 1, h->stream));
   return LBM_OK;
 }
 

@@ -71,6 +71,7 @@ struct lbm_cube {
   double *mon_dev = nullptr;    // chunk monitor sums
   double *aux_dev = nullptr;    // on-demand sums
   double *mon_host = nullptr;   // pinned
+  HostStage stage;              // large results on their way to the host
   double *tmp = nullptr;        // FP64 transfer scratch
   size_t tmp_doubles = 0;
   hipStream_t stream = nullptr, own_stream = nullptr, cap_stream = nullptr;
@@ -336,6 +337,7 @@ int lbm3d_destroy(lbm3d_t h) {
                   (void *)h->mon_dev, (void *)h->aux_dev, (void *)h->tmp})
     if (p) (void)hipFree(p);
   if (h->mon_host) (void)hipHostFree(h->mon_host);
+  h->stage.release();
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
   if (h->own_stream) (void)hipStreamDestroy(h->own_stream);
   delete h;
@@ -554,11 +556,10 @@ int lbm3d_moments(lbm3d_t h, double *rho, double *ux, double *uy, double *uz) {
                        (const float *)h->buf[h->cur], h->nx, h->ny, h->nz, h->pitch, h->plane,
                        d[0], d[1], d[2], d[3]);
   HIPC(hipGetLastError());
-  double *outs[4] = {rho, ux, uy, uz};
-  for (int k = 0; k < 4; ++k)
-    if (outs[k])
-      HIPC(hipMemcpyAsync(outs[k], d[k], n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPC(hipStreamSynchronize(h->stream));
+  double *dst[4] = {rho, ux, uy, uz};
+  CopyOut outs[4];
+  for (int k = 0; k < 4; ++k) outs[k] = {dst[k], d[k], n * sizeof(double)};
+  HIPC(h->stage.copy(outs, 4, h->stream));
   return LBM_OK;
 }
 
@@ -599,8 +600,8 @@ int lbm3d_get_populations(lbm3d_t h, double *fstar) {
                        (const float *)h->buf[h->cur], h->nx, h->ny, h->nz, h->pitch, h->plane,
                        h->tmp);
   HIPC(hipGetLastError());
-  HIPC(hipMemcpyAsync(fstar, h->tmp, 19 * n * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIPC(hipStreamSynchronize(h->stream));
+  const CopyOut out{fstar, h->tmp, 19 * n * sizeof(double)};
+  HIPC(h->stage.copy(&out, 1, h->stream));
   return LBM_OK;
 }
 

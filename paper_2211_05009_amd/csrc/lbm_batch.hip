@@ -53,6 +53,7 @@ struct lbm_batch {
   double *mon_dev = nullptr;            // [n][3] chunk monitors
   double *aux_dev = nullptr;            // on-demand reductions
   double *mon_host = nullptr;           // pinned [n][3] + 4
+  HostStage stage;                      // large results on their way to the host
   double *tmp = nullptr;
   size_t tmp_doubles = 0;
   std::vector<char> active;
@@ -497,6 +498,7 @@ int lbm_batch_destroy(lbm_batch_t b) {
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   if (b->mon_host) (void)hipHostFree(b->mon_host);
+  b->stage.release();
   if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
   if (b->own_stream) (void)hipStreamDestroy(b->own_stream);
   delete b;
@@ -805,11 +807,9 @@ int lbm_batch_moments(lbm_batch_t b, int k, double *rho, double *ux, double *uy)
     hipLaunchKernelGGL((k_moments<float, true>), dim3((n + 255) / 256), dim3(256), 0, b->stream,
                        (const float *)b->buf[cbuf(b, k)] + b->base[k], g, d[0], d[1], d[2]);
   HIPC(hipGetLastError());
-  double *outs[3] = {rho, ux, uy};
-  for (int j = 0; j < 3; ++j)
-    if (outs[j])
-      HIPC(hipMemcpyAsync(outs[j], d[j], n * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-  HIPC(hipStreamSynchronize(b->stream));
+  const CopyOut outs[3] = {
+      {rho, d[0], n * sizeof(double)}, {ux, d[1], n * sizeof(double)}, {uy, d[2], n * sizeof(double)}};
+  HIPC(b->stage.copy(outs, 3, b->stream));
   return LBM_OK;
 }
 
@@ -826,8 +826,8 @@ int lbm_batch_get_populations(lbm_batch_t b, int k, double *f) {
     hipLaunchKernelGGL((k_get_pop<float, true>), dim3((n + 255) / 256), dim3(256), 0,
                        b->stream, (const float *)b->buf[cbuf(b, k)] + b->base[k], g, b->tmp);
   HIPC(hipGetLastError());
-  HIPC(hipMemcpyAsync(f, b->tmp, 9 * n * sizeof(double), hipMemcpyDeviceToHost, b->stream));
-  HIPC(hipStreamSynchronize(b->stream));
+  const CopyOut out{f, b->tmp, 9 * n * sizeof(double)};
+  HIPC(b->stage.copy(&out, 1, b->stream));
   return LBM_OK;
 }
 

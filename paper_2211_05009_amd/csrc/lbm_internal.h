@@ -7,6 +7,7 @@
 #include <string>
 
 #include "../../include/lbm.h"
+#include "host_copy.h"
 
 // Record a message for lbm_last_error() and return `code`.
 int lbm_fail(int code, const char *fmt, ...);
@@ -68,6 +69,7 @@ struct lbm_cavity {
   double *mon_dev = nullptr;    // chunk monitor sums: sum(rho-1), num, den
   double *aux_dev = nullptr;    // on-demand reductions
   double *mon_host = nullptr;   // pinned
+  lbm::HostStage stage;         // large results on their way to the host
   void *vortex_host = nullptr;  // pinned results of a vortex call, from its first use on
   double *tmp = nullptr;        // FP64 transfer scratch
   size_t tmp_doubles = 0;
