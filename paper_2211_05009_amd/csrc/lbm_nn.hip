@@ -117,11 +117,16 @@ template <int MODE, int RT, int WR, int WC>
 void conv_tile(const ConvArgs &a, hipStream_t st) {
   const int ntx = a.w / (16 * WC), nty = (a.h + RT * WR - 1) / (RT * WR);
   const dim3 grid(a.n * ntx * nty * ((MODE == FWD ? a.co : a.ci) / 32));
-  if ((MODE == FWD ? a.ci : a.co) == 32)
-    hipLaunchKernelGGL((k_conv_tile<MODE, RT, WR, WC, true>), grid, dim3(256), 0, st, a, ntx, nty);
-  else
-    hipLaunchKernelGGL((k_conv_tile<MODE, RT, WR, WC, false>), grid, dim3(256), 0, st, a, ntx,
-                       nty);
+  auto go = [&](auto one, auto ends) {
+    hipLaunchKernelGGL((k_conv_tile<MODE, RT, WR, WC, decltype(one)::value, decltype(ends)::value>),
+                       grid, dim3(256), 0, st, a, ntx, nty);
+  };
+  using yes = std::true_type;
+  using no = std::false_type;
+  if ((MODE == FWD ? a.ci : a.co) > 32) return go(no{}, no{});
+  if constexpr (MODE == FWD && WC == 2)
+    if (a.enc || a.head) return go(yes{}, yes{});
+  go(yes{}, no{});
 }
 
 // Whether conv_fd takes k_conv_tile for a w x h image: widths of whole tiles,
@@ -415,35 +420,21 @@ uint16_t *bptr(lbm_surrogate *s, uint16_t *base, const View &v) {
   return base + s->act_off[v.buf];
 }
 
-// Encode (Re, Ar) pairs into the input canvas: channel 0 = cavity mask
-// (rows y < round(128 Ar)), 1 = (x + 1/2)/128, 2 = (y + 1/2)/128,
-// 3 = Re / 3000, 4 = Ar / 2, channels 5-31 zero.
-// One thread per 16-byte vector (8 channels) of a pixel, so a wavefront
-// stores 1 KB of contiguous memory: vector 0 holds channels 0-4, vectors 1-3
-// are zero.
+// Encode (Re, Ar) pairs into the input canvas (encode_vec).  One thread per
+// 16-byte vector (8 channels) of a pixel, so a wavefront stores 1 KB of
+// contiguous memory: vector 0 holds channels 0-4, vectors 1-3 are zero.
+// Training only (the weight gradient of the first layer reads the canvas); a
+// forecast's first layer encodes for itself.
 __global__ void k_encode(const double *ra, int n, uint16_t *x) {
   const long long t = blockIdx.x * 256LL + threadIdx.x;
   if (t >= (long long)n * kH * kW * 4) return;
   const long long i = t >> 2;   // pixel
   uint4 v = make_uint4(0, 0, 0, 0);
   if ((t & 3) == 0) {
-    const int b = i / (kH * kW), r = i % (kH * kW), y = r / kW, xx = r % kW;
-    const double re = ra[2 * b], ar = ra[2 * b + 1];
-    const int ny = (int)rint(128.0 * ar);
-    const float ch[kInCh] = {y < ny ? 1.f : 0.f, (xx + 0.5f) / 128.f, (y + 0.5f) / 128.f,
-                             (float)(re / 3000.0), (float)(ar / 2.0)};
-    static_assert(kInCh == 5, "channels 0-4 packed below");
-    v = make_uint4(f2bf(ch[0]) | ((uint32_t)f2bf(ch[1]) << 16),
-                   f2bf(ch[2]) | ((uint32_t)f2bf(ch[3]) << 16), f2bf(ch[4]), 0);
+    const int b = i / (kH * kW), r = i % (kH * kW);
+    v = encode_vec(ra[2 * b], ra[2 * b + 1], r % kW, r / kW);
   }
   ((uint4 *)x)[t] = v;   // the canvas is dense, 32 channels
-}
-
-// Head output channels 0..2 -> FP32 [n][H][W][3].
-__global__ void k_extract(const uint16_t *y, long long npix, float *out) {
-  const long long i = blockIdx.x * 256LL + threadIdx.x;
-  if (i >= npix * kOutCh) return;
-  out[i] = bf2f(y[(i / kOutCh) * 32 + i % kOutCh]);
 }
 
 // Bilinear map of sample 0's prediction (rows < ny_c of the canvas) onto an
@@ -475,7 +466,12 @@ __global__ void k_to_lattice(const float *p3, int ny_c, int nx, int ny, double u
   uy[k] = u_lid * v[2];
 }
 
-int forward(lbm_surrogate *s, int n) {
+// The network on n samples.  With enc (their (Re, Ar) pairs on the device) the
+// first layer encodes them itself instead of reading the canvas; with head the
+// last one also writes its first three channels there in FP32.  Both are done by
+// k_conv_tile, which serves the canvas at full resolution.
+int forward(lbm_surrogate *s, int n, const double *enc, float *head) {
+  static_assert(kInCh == 5 && kOutCh == 3 && kW == 128 && kH % 2 == 0, "k_conv_tile's ends");
   hipStream_t st = s->stream;
   for (const Op &o : s->ops) {
     const int h = level_h(o.level), w = level_w(o.level);
@@ -493,6 +489,8 @@ int forward(lbm_surrogate *s, int n) {
       a.wf = s->wbf + o.woff;
       a.bias = s->w + o.boff;
       a.relu = o.relu;
+      if (&o == &s->ops.front()) a.enc = enc;
+      if (&o == &s->ops.back()) a.head = head;
       a.out = bptr(s, s->act, o.out);
       a.os = o.out.cs;
       a.oo = o.out.co;
@@ -658,7 +656,8 @@ hipError_t pack_weights(lbm_surrogate *s) {
   return hipGetLastError();
 }
 
-int encode(lbm_surrogate *s, int n, const double *re, const double *ar) {
+// Check the (Re, Ar) pairs of a call and send them to the device.
+int send_pairs(lbm_surrogate *s, int n, const double *re, const double *ar) {
   std::vector<double> ra(2 * n);
   for (int b = 0; b < n; ++b) {
     if (!(re[b] > 0.0) || !(ar[b] > 0.0) || !std::isfinite(re[b]) || 128.0 * ar[b] > kH + 0.5)
@@ -669,10 +668,6 @@ int encode(lbm_surrogate *s, int n, const double *re, const double *ar) {
   }
   HIPC(hipMemcpyAsync(s->rearr, ra.data(), 2 * n * sizeof(double), hipMemcpyHostToDevice,
                       s->stream));
-  const View x0{0, 32, 0};
-  hipLaunchKernelGGL(k_encode, dim3(blocks_for((long long)n * kH * kW * 4)), dim3(256), 0, s->stream,
-                     s->rearr, n, bptr(s, s->act, x0));
-  HIPC(hipGetLastError());
   return LBM_OK;
 }
 
@@ -950,14 +945,10 @@ int lbm_sur_get_params(lbm_sur_t s, float *params_host, float *grads_host) {
 int lbm_sur_forward(lbm_sur_t s, int n, const double *re, const double *ar, float *out_dev) {
   if (!s || !re || !ar || !out_dev) return lbm_fail(LBM_EINVAL, "NULL argument");
   if (n < 1 || n > s->nmax) return lbm_fail(LBM_EINVAL, "n = %d outside [1, %d]", n, s->nmax);
-  int rc = encode(s, n, re, ar);
+  int rc = send_pairs(s, n, re, ar);
   if (rc) return rc;
-  rc = forward(s, n);
+  rc = forward(s, n, s->rearr, out_dev);
   if (rc) return rc;
-  const long long npix = (long long)n * kH * kW;
-  hipLaunchKernelGGL(k_extract, dim3(blocks_for(npix * kOutCh)), dim3(256), 0, s->stream,
-                     bptr(s, s->act, head_view(s)), npix, out_dev);
-  HIPC(hipGetLastError());
   HIPC(hipStreamSynchronize(s->stream));
   return LBM_OK;
 }
@@ -970,9 +961,13 @@ int lbm_sur_train_step(lbm_sur_t s, int n, const double *re, const double *ar,
   if (!(lr >= 0.0) || !std::isfinite(lr)) return lbm_fail(LBM_EINVAL, "lr = %g", lr);
   double count = 0.0;
   for (int b = 0; b < n; ++b) count += 128.0 * std::rint(128.0 * ar[b]);
-  int rc = encode(s, n, re, ar);
+  int rc = send_pairs(s, n, re, ar);
   if (rc) return rc;
-  rc = forward(s, n);
+  const View x0{0, 32, 0};
+  hipLaunchKernelGGL(k_encode, dim3(blocks_for((long long)n * kH * kW * 4)), dim3(256), 0,
+                     s->stream, s->rearr, n, bptr(s, s->act, x0));
+  HIPC(hipGetLastError());
+  rc = forward(s, n, nullptr, nullptr);
   if (rc) return rc;
   const long long npix = (long long)n * kH * kW;
   HIPC(hipMemsetAsync(s->loss_dev, 0, sizeof(float), s->stream));

@@ -41,6 +41,17 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
 
 enum { FWD = 0, DGRAD = 1, WGRAD = 2 };
 
+// Channels 0 .. 7 of pixel (x, y) of the encoded input canvas: 0 = cavity mask
+// (rows y < round(128 Ar)), 1 = (x + 1/2) / 128, 2 = (y + 1/2) / 128, 3 =
+// Re / 3000, 4 = Ar / 2, the others (and channels 8 .. 31) zero.
+__device__ __forceinline__ uint4 encode_vec(double re, double ar, int x, int y) {
+  const int ny = (int)rint(128.0 * ar);
+  const float ch[5] = {y < ny ? 1.f : 0.f, (x + 0.5f) / 128.f, (y + 0.5f) / 128.f,
+                       (float)(re / 3000.0), (float)(ar / 2.0)};
+  return make_uint4(f2bf(ch[0]) | ((uint32_t)f2bf(ch[1]) << 16),
+                    f2bf(ch[2]) | ((uint32_t)f2bf(ch[3]) << 16), f2bf(ch[4]), 0);
+}
+
 struct ConvArgs {
   int n, h, w, ci, co;
   const uint16_t *x;   // FWD / WGRAD: input activations; DGRAD: output gradient
@@ -63,6 +74,12 @@ struct ConvArgs {
   uint16_t *pool_out;  // its 2 x 2 average pool, dense [n][h/2][w/2][co]
   uint16_t *up_out;    // its nearest 2x upsampling, a slice (ups, upo) of
   int ups, upo;        // [n][2h][2w]
+  // FWD, k_conv_tile (optional), the network's ends: the input is the encoding
+  // of an image's (Re, Ar) pair enc[2 b], enc[2 b + 1] and x is not read (32
+  // input channels); channels 0 .. 2 of the rounded output also go, as FP32,
+  // to head [n][h][w][3]
+  const double *enc;
+  float *head;
   int kchunk;          // WGRAD: pixels per block (multiple of 32)
   float *part;         // WGRAD: per-chunk partials [gridDim.z][9 ci][co], added
                        // into GW in chunk order by k_sum_parts (deterministic)
@@ -257,6 +274,8 @@ __global__ __launch_bounds__(256) void k_conv_mn(ConvArgs a) {
 // patch and weights staged through LDS): forward 248 -> 182 us, input gradient
 // 270 -> 188 us; 384 > 128 channels at 32 x 64 29.0 -> 17.0 us (850 TFLOP/s),
 // 32 > 32 at 128 x 256 14.5 -> 10.5 us (3.2 TB/s, 6.7 us at a copy's rate).
+// The network's ends, without the encoding and extracting kernels around them:
+// a forecast of 8 samples 228 -> 216 us.
 
 // the value of the neighbouring lane (lane ^ 1)
 __device__ __forceinline__ float lane_xor1(float v) {
@@ -273,10 +292,13 @@ __device__ __forceinline__ void swap16(float &a, float &b) {
   b = __uint_as_float(r[1]);
 }
 
-template <int MODE, int RT, int WR, int WC, bool ONE>
+// ENDS: with ConvArgs enc and head (the others carry no code for them: it costs
+// registers, and 2 % of a training step).
+template <int MODE, int RT, int WR, int WC, bool ONE, bool ENDS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ONE ? 4 : 2))) void
 k_conv_tile(ConvArgs a, int ntx, int nty) {
   static_assert(WR * WC == 2 && RT % 2 == 0, "two waves along the pixels");
+  static_assert(!ENDS || (MODE == FWD && ONE), "the network's ends");
   constexpr int BR = RT * WR, BC = 16 * WC;
   // patch rows of a multiple of 4 pixels, so that a row's columns have the
   // same banks whatever the row
@@ -352,8 +374,20 @@ k_conv_tile(ConvArgs a, int ntx, int nty) {
   bf16x8 w0[9], w1[9];
   {
     const auto rs = image(true);
+    if (ENDS && a.enc) {
+      const double re = a.enc[2 * img], ar = a.enc[2 * img + 1];
 #pragma unroll
-    for (int u = 0; u < PV; ++u) rp[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, poff[u], 0, 0);
+      for (int u = 0; u < PV; ++u) {
+        const int pp = (tid + 256 * u) >> 2, py = pp / PW;
+        const uint4 v = encode_vec(re, ar, x0 + pp - py * PW - 1, y0 + py - 1);
+        const bool on = pkq == 0 && poff[u] != 0x7ffffff0;
+        rp[u] = on ? u32x4{v.x, v.y, v.z, v.w} : u32x4{0, 0, 0, 0};
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < PV; ++u)
+        rp[u] = __builtin_amdgcn_raw_buffer_load_b128(rs, poff[u], 0, 0);
+    }
 #pragma unroll
     for (int t = 0; t < 9; ++t) w0[t] = *(const bf16x8 *)(wsrc + t * (size_t)wtap + wlane);
 #pragma unroll
@@ -470,6 +504,11 @@ k_conv_tile(ConvArgs a, int ntx, int nty) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) pv[e] = f2bf(v[e]);
       *(uint4 *)o = pk;
+      if (ENDS && a.head && ch == 0) {
+        float *hd = a.head + ((size_t)(img * a.h + y) * a.w + x) * 3;
+#pragma unroll
+        for (int e = 0; e < 3; ++e) hd[e] = bf2f(pv[e]);
+      }
       if (MODE == FWD && a.up_out) {   // the 2 x 2 copies at twice the resolution
         uint16_t *u = a.up_out +
                       ((size_t)(img * 2 * a.h + 2 * y) * (2 * a.w) + 2 * x) * a.ups + a.upo + ch;

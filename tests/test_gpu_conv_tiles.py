@@ -75,3 +75,21 @@ def test_network_outputs_do_not_depend_on_the_batch():
         sur.forward(re[b:b + 1], ar[b:b + 1], one)
         assert torch.equal(one[0], out[b])
     sur.close()
+
+
+@pytest.mark.parametrize("n", [1, 5, 16])
+def test_forecast_equals_the_training_forward(n):
+    """A forecast's first layer encodes (Re, Ar) itself and its last one writes
+    the result; training reads the encoded canvas.  Against its own forecast as
+    the target, a training step's loss is exactly zero."""
+    import torch
+    from paper_2211_05009_amd import lbm
+    sur = lbm.Surrogate(max_batch=16)
+    sur.set_params(S.he_init(2))
+    re, ar = np.linspace(150.0, 2500.0, n), np.linspace(0.4, 1.9, n)
+    out = torch.full((n, 256, 128, 3), np.nan, dtype=torch.float32, device="cuda")
+    sur.forward(re, ar, out)
+    mask = torch.ones((n, 256, 128), dtype=torch.float32, device="cuda")
+    assert float(out.abs().max()) > 0
+    assert sur.train_step(re, ar, out, mask, lr=0.0, apply_update=False) == 0.0
+    sur.close()
