@@ -52,6 +52,8 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
   for (int k = 0; k < n; ++k)
     if (outs[k].dst) total += outs[k].bytes;
   staged = total >= kMinBytes;
+  const bool large = total >= kLargeBytes;
+  const size_t chunk = large ? kChunkBytes : kSmallChunkBytes;
   for (int k = 0; k < n && staged; ++k)
     if (outs[k].dst) staged = pageable(outs[k].dst);
   std::vector<CopyOut> chunks;
@@ -59,9 +61,9 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
   if (staged) {
     try {
       for (int k = 0; k < n; ++k)
-        for (size_t o = 0; outs[k].dst && o < outs[k].bytes; o += kChunkBytes)
+        for (size_t o = 0; outs[k].dst && o < outs[k].bytes; o += chunk)
           chunks.push_back({(char *)outs[k].dst + o, (const char *)outs[k].src + o,
-                            std::min(kChunkBytes, outs[k].bytes - o)});
+                            std::min(chunk, outs[k].bytes - o)});
       threads.reserve(kThreads);
       staged = ensure();
     } catch (...) {
@@ -92,7 +94,8 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
   };
   if (staged) {
     const unsigned hw = std::thread::hardware_concurrency();
-    const int want = hw ? std::min<int>(kThreads, (int)hw) : kThreads;
+    const int most = large ? kThreads : kThreads / 2;
+    const int want = hw ? std::min<int>(most, (int)hw) : most;
     try {
       for (int k = 0; k < want; ++k) threads.emplace_back(work, k);
     } catch (...) {   // as many as there are

@@ -1,5 +1,6 @@
 """GPU tests of the staged device-to-host copies (csrc/host_copy.hip): results
-from 16 MB on go through pinned buffers and several threads, in 4 MB chunks.
+from 4 MB on go through pinned buffers and several threads, in 512 KB chunks,
+from 16 MB on in 4 MB ones.
 
 The same bytes have to arrive as by the device entry point or by a read of
 every site, whatever the size of the last chunk, for fresh, unaligned,
@@ -19,8 +20,9 @@ def _device_moments(torch, c, ny, nx):
     return [x.cpu().numpy() for x in d]
 
 
-# 3 fields of 8 nx ny bytes: just below 16 MB, 16 MB and a bit, ragged chunks
-@pytest.mark.parametrize("nx,ny", [(700, 998), (700, 1000), (1023, 1025), (1500, 1111)])
+# 3 fields of 8 nx ny bytes: just below and above 4 MB and 16 MB, ragged chunks
+@pytest.mark.parametrize("nx,ny", [(419, 417), (419, 418), (500, 500), (700, 998),
+                                   (700, 1000), (1023, 1025), (1500, 1111)])
 def test_moments_match_the_device_entry_point(nx, ny):
     import torch
     from paper_2211_05009_amd import lbm
