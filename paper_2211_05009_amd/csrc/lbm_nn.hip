@@ -88,7 +88,25 @@ inline SumSeg sum_seg(const float *part, long long n, float *out, int nparts, bo
   int g = 1;
   while (g < 16 && g < nparts && n4 * g < 65536) g *= 2;
   const int V = 256 / g;
-  return SumSeg{part, n, out, g, (int)((n4 + V - 1) / V), add ? 1 : 0};
+  return SumSeg{part, n, out, nparts, g, (int)((n4 + V - 1) / V), add ? 1 : 0};
+}
+
+// Launch the collected sums and empty the table.
+//
+// The network's layers are added in groups of 64 MB of partials beside the
+// largest layer's own (kPartGroup; at most eight layers): a sum after every
+// layer took 5.6 us, a good part of it launch and a last round of blocks.  A
+// training step at batch 8: a sum per layer 837 us, groups within the largest
+// layer's buffer 810, with 32 MB more 813, 64 MB 794, 256 MB 797 (one launch
+// less, but the last group waits behind the pass).
+constexpr size_t kPartGroup = 16u << 20;   // floats
+hipError_t sums_launch(SumTable &tb, hipStream_t st) {
+  if (tb.count == 0) return hipSuccess;
+  int blocks = 0;
+  for (int k = 0; k < tb.count; ++k) blocks += tb.s[k].blocks;
+  hipLaunchKernelGGL(k_sum_parts_v4, dim3(blocks), dim3(256), 0, st, tb);
+  tb.count = 0;
+  return hipGetLastError();
 }
 
 template <int W, int U>
@@ -102,7 +120,8 @@ void wgrad_rows(const ConvArgs &a, const RowsPlan &p, float *bpart, hipStream_t 
                        p.rows, bpart);
 }
 
-hipError_t wgrad_launch(const ConvArgs &a, float *gbias, hipStream_t st, bool add = true);
+hipError_t wgrad_launch(const ConvArgs &a, float *gbias, hipStream_t st, bool add = true,
+                        SumTable *later = nullptr);
 
 // One forward or input-gradient pass with tile shape <WM, WN, TM, TN>.
 template <int MODE, int WM, int WN, int TM, int TN>
@@ -223,8 +242,11 @@ hipError_t bias_grad_launch(const uint16_t *g, int gs, int go, long long npix, i
 // set also its bias gradient into gbias, added to what they hold (add) or
 // replacing it: k_wgrad_rows where the width allows (the bias sums then
 // ride along with its loads of GY), else k_wgrad and k_bias_grad.  Partials
-// in a.part (wgrad_part_floats).
-hipError_t wgrad_launch(const ConvArgs &a, float *gbias, hipStream_t st, bool add) {
+// in a.part (wgrad_part_floats).  With `later` (room for two segments) the
+// sums may be left to the caller's sums_launch; the partials have to stay
+// until then.
+hipError_t wgrad_launch(const ConvArgs &a, float *gbias, hipStream_t st, bool add,
+                        SumTable *later) {
   const RowsPlan p = wgrad_rows_plan(a.n, a.h, a.w, a.ci, a.co);
   const bool v4 = (uintptr_t)a.out % 16 == 0 && (!gbias || (uintptr_t)gbias % 16 == 0);
   if (!add && !(p.ok && v4)) {   // the paths below add: clear the targets first
@@ -247,11 +269,11 @@ hipError_t wgrad_launch(const ConvArgs &a, float *gbias, hipStream_t st, bool ad
     default: wgrad_rows<128, kRowsPix / 128>(a, p, bpart, st); break;
   }
   if (v4) {   // mn and co are multiples of 4 (channel counts multiples of 32)
-    const SumSeg s1 = sum_seg(a.part, mn, (float *)a.out, p.nz, add);
-    const SumSeg s2 =
-        gbias ? sum_seg(bpart, a.co, gbias, p.nz, add) : SumSeg{nullptr, 0, nullptr, 1, 0, 0};
-    hipLaunchKernelGGL(k_sum_parts_v4, dim3(s1.blocks + s2.blocks), dim3(256), 0, st, s1, s2,
-                       p.nz);
+    SumTable own{};
+    SumTable &tb = later ? *later : own;
+    tb.s[tb.count++] = sum_seg(a.part, mn, (float *)a.out, p.nz, add);
+    if (gbias) tb.s[tb.count++] = sum_seg(bpart, a.co, gbias, p.nz, add);
+    if (!later) return sums_launch(tb, st);
   } else {
     hipLaunchKernelGGL(k_sum_parts, dim3(blocks_for(mn, kSumOut)), dim3(256), 0, st, a.part, p.nz,
                        mn, (float *)a.out);
@@ -316,6 +338,7 @@ struct lbm_surrogate {
   float *target = nullptr, *mask = nullptr, *out3 = nullptr;
   float *loss_dev = nullptr, *loss_host = nullptr;
   float *part = nullptr;   // partials of the split reductions (see k_sum_parts)
+  size_t part_floats = 0;
   // ReLU gradients fused into the pass that writes the last contribution to
   // a ReLU conv's output gradient: mask_of[j] = that conv for op j (else -1),
   // relu_fused[p] set for such a conv p (its separate ReLU pass is skipped)
@@ -577,6 +600,10 @@ int backward(lbm_surrogate *s, int n) {
         (void)hipStreamWaitEvent(s->stream, s->join, 0);
     }
   } join{s};
+  // The partials of consecutive layers lie one after another in s->part and
+  // are added by one launch per group.
+  SumTable sums{};
+  size_t used = 0;
   // every conv's weight and bias gradients are written once (not added)
   for (int k = (int)s->ops.size() - 1; k >= 0; --k) {
     const Op &o = s->ops[k];
@@ -604,10 +631,16 @@ int backward(lbm_surrogate *s, int n) {
       a.go = o.out.co;
       a.out = s->gw + o.woff;
       a.kchunk = wgrad_kchunk(n, h, w, o.ci, o.co);
-      a.part = s->part;   // used by the side stream only until the join
+      const size_t need = wgrad_part_floats(n, h, w, o.ci, o.co);
+      if (used + need > s->part_floats || sums.count + 2 > kSumSegs) {
+        HIPC(sums_launch(sums, s->side));
+        used = 0;
+      }
+      a.part = s->part + used;   // used by the side stream only until the join
       HIPC(hipEventRecord(s->fork, st));
       HIPC(hipStreamWaitEvent(s->side, s->fork, 0));
-      HIPC(wgrad_launch(a, s->gw + o.boff, s->side, false));
+      HIPC(wgrad_launch(a, s->gw + o.boff, s->side, false, &sums));
+      used += (need + 3) / 4 * 4;
       if (k > 0) {   // the network input needs no gradient
         ConvArgs d{};
         d.n = n;
@@ -642,6 +675,7 @@ int backward(lbm_surrogate *s, int n) {
       HIPC(hipGetLastError());
     }
   }
+  HIPC(sums_launch(sums, s->side));
   return LBM_OK;
 }
 
@@ -863,7 +897,8 @@ int lbm_sur_create(int max_batch, lbm_sur_t *out) {
     if (o.type == OP_CONV)
       part_floats = std::max(part_floats, wgrad_part_floats(max_batch, level_h(o.level),
                                                             level_w(o.level), o.ci, o.co));
-  if (e == hipSuccess) e = hipMalloc(&s->part, part_floats * sizeof(float));
+  s->part_floats = part_floats + kPartGroup;
+  if (e == hipSuccess) e = hipMalloc(&s->part, s->part_floats * sizeof(float));
   if (e == hipSuccess) e = hipMalloc(&s->wbf, s->nparams * 2);
   if (e == hipSuccess) e = hipMalloc(&s->wbd, s->nparams * 2);
   if (e == hipSuccess) e = hipMemsetAsync(s->wbf, 0, s->nparams * 2, s->stream);

@@ -999,29 +999,35 @@ __global__ __launch_bounds__(256) void k_sum_scalar(const float *part, int npart
   if (threadIdx.x == 0) out[0] += sh[0];
 }
 
-// Partial sums of a layer's weight and bias gradients in one launch:
-// out[i] (+)= sum over k of part[k][i] for each of two segments (blocks below
-// s1.blocks take segment 1).  A thread adds 4 consecutive outputs (16-byte
-// loads); the block's `groups` thread groups (a power of two dividing 256)
-// take k = g, g + groups, ... in order and the group sums are added in
-// group order, so the result is fixed for a given shape.  Many groups
-// serve few outputs with many partials, one group many outputs.  n, the
+// Partial sums of up to eight layers' weight and bias gradients in one launch:
+// out[i] (+)= sum over k of part[k][i] for each segment of the table (blocks
+// below s[0].blocks take segment 0, and so on).  A thread adds 4 consecutive
+// outputs (16-byte loads); the block's `groups` thread groups (a power of two
+// dividing 256) take k = g, g + groups, ... in order and the group sums are
+// added in group order, so the result is fixed for a given shape.  Many
+// groups serve few outputs with many partials, one group many outputs.  n, the
 // pointers' element offsets: multiples of 4.
 struct SumSeg {
   const float *part;
   long long n;
   float *out;
-  int groups, blocks;
+  int nparts, groups, blocks;
   int add;   // 1: out += sum, 0: out = sum
 };
-__global__ __launch_bounds__(256) void k_sum_parts_v4(SumSeg s1, SumSeg s2, int nparts) {
-  const bool first = (int)blockIdx.x < s1.blocks;
-  const float *part = first ? s1.part : s2.part;
-  float *out = first ? s1.out : s2.out;
-  const long long n4 = (first ? s1.n : s2.n) / 4;
-  const int G = first ? s1.groups : s2.groups, V = 256 / G;
-  const bool add = first ? s1.add : s2.add;
-  const int b = first ? blockIdx.x : blockIdx.x - s1.blocks;
+constexpr int kSumSegs = 16;
+struct SumTable {
+  int count;
+  SumSeg s[kSumSegs];
+};
+__global__ __launch_bounds__(256) void k_sum_parts_v4(SumTable tb) {
+  int seg = 0, b = blockIdx.x;
+  while (seg + 1 < tb.count && b >= tb.s[seg].blocks) b -= tb.s[seg++].blocks;
+  const SumSeg &sg = tb.s[seg];
+  const float *part = sg.part;
+  float *out = sg.out;
+  const int nparts = sg.nparts, G = sg.groups, V = 256 / G;
+  const long long n4 = sg.n / 4;
+  const bool add = sg.add;
   const int g = threadIdx.x / V, vi = threadIdx.x - g * V;
   const long long i = (long long)b * V + vi;   // vector index
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);

@@ -93,3 +93,23 @@ def test_forecast_equals_the_training_forward(n):
     assert float(out.abs().max()) > 0
     assert sur.train_step(re, ar, out, mask, lr=0.0, apply_update=False) == 0.0
     sur.close()
+
+
+def test_gradients_do_not_depend_on_the_partials_buffer():
+    """The partial sums of consecutive layers are added in groups that follow
+    from the handle's buffer (its largest batch): the same gradients, bit for
+    bit."""
+    import torch
+    from paper_2211_05009_amd import lbm
+    gen = torch.Generator().manual_seed(5)
+    target = torch.randn(2, 256, 128, 3, generator=gen).cuda()
+    mask = torch.ones((2, 256, 128), dtype=torch.float32, device="cuda")
+    grads = []
+    for nmax in (2, 16):
+        sur = lbm.Surrogate(max_batch=nmax)
+        sur.set_params(S.he_init(3))
+        for _ in range(2):
+            sur.train_step([900.0, 400.0], [1.1, 0.7], target, mask, lr=0.0, apply_update=False)
+        grads.append(sur.get_params(with_grads=True)[1])
+        sur.close()
+    assert np.any(grads[0] != 0) and np.array_equal(grads[0], grads[1])
