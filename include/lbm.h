@@ -193,7 +193,8 @@ int lbm_get_option(lbm_t h, int option, int64_t *value);
  * counter and monitors exactly as before the call.  Must be called at a
  * multiple of 100 steps.  If use_cache is non-zero and the file named by the
  * environment variable LBM_TUNE_CACHE holds an entry for this device,
- * storage type and lattice, that entry is applied without timing
+ * storage type and lattice, written by a library with the same table of
+ * shapes, that entry is applied without timing
  * (*ms_per_step = NaN); a timed result is appended to that file.  Outputs
  * may be NULL.  The shapes give bit-identical results.
  */

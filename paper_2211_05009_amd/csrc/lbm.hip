@@ -87,7 +87,8 @@ double lbm_wall_seconds() {
 }
 
 // ------------------------------------------------------------ tune cache
-std::string tune_key(const char *kind, int dtype, long long a, long long b) {
+std::string tune_key(const char *kind, int shapes, int revision, int dtype, long long a,
+                     long long b) {
   char arch[64] = "unknown";
   int dev = 0;
   hipDeviceProp_t prop;
@@ -97,7 +98,7 @@ std::string tune_key(const char *kind, int dtype, long long a, long long b) {
       if (*c == ' ' || *c == ':') *c = '_';
   }
   char buf[192];
-  std::snprintf(buf, sizeof buf, "%s|%s|%s|%lld|%lld", arch, kind,
+  std::snprintf(buf, sizeof buf, "%s|%s/%d.%d|%s|%lld|%lld", arch, kind, shapes, revision,
                 dtype == LBM_F64 ? "f64" : "f32s", a, b);
   return buf;
 }
@@ -130,6 +131,7 @@ void tune_cache_store(const std::string &key, int variant) {
 // element, block 64 x BY.  Temporal (k_step_tb, variants 12-32): K steps per
 // launch on TX x TY tiles held in LDS.  All give bit-identical results.
 static const int kNumVariants = 33;
+static const int kVariantsRevision = 2;   // see tune_key
 
 // Steps applied by one launch of variant v.
 static int steps_per_launch(int v) {
@@ -211,6 +213,7 @@ static int default_variant(int nx, int ny, int dtype) {
 // on a tile chosen from the lattice (nee_tile6); K = 5 on 32 x 32 (FP64 K = 2
 // on 16 x 32).
 static const int kNumNeeVariants = 8;
+static const int kNeeVariantsRevision = 2;   // see tune_key
 static const int kDefaultNeeVariant = 6;
 
 // Tile of NEE shape 6 (K = 4, two LDS buffers, one site of the first window
@@ -1107,8 +1110,10 @@ int lbm_autotune(lbm_t h, int chunks, int use_cache, int *best_variant, double *
   if (chunks < 1 || chunks > 10000)
     return lbm_fail(LBM_EINVAL, "chunks = %d outside [1, 10000]", chunks);
   if (h->t % kChunk != 0) return lbm_fail(LBM_EINVAL, "autotune only at a multiple of 100 steps");
+  const bool nee = h->wall == LBM_WALL_NEE;
   const std::string key =
-      tune_key(h->wall == LBM_WALL_NEE ? "single-nee" : "single", h->dtype, h->nx, h->ny);
+      tune_key(nee ? "single-nee" : "single", num_variants(h),
+               nee ? kNeeVariantsRevision : kVariantsRevision, h->dtype, h->nx, h->ny);
   const int cached = use_cache ? tune_cache_lookup(key) : -1;
   if (cached >= 0 && cached < num_variants(h)) {
     if (best_variant) *best_variant = cached;

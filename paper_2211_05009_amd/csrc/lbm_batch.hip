@@ -96,6 +96,7 @@ const Shape kShapes[] = {
     {2, 0, 0, 10, 32, 32, 32, 16}, {2, 0, 0, 2, 32, 32, 32, 32}, {2, 0, 0, 5, 64, 32, 64, 16},
     {2, 0, 0, 5, 32, 16, 32, 16}, {2, 0, 0, 5, 32, 16, 32, 16}};
 const int kNumShapes = 20;
+const int kShapesRevision = 2;   // see tune_key
 
 int shape_steps(int v) { return kShapes[v].k; }
 
@@ -950,7 +951,8 @@ int lbm_batch_autotune(lbm_batch_t b, int chunks, int use_cache, int *best_varia
   if (chunks < 1 || chunks > 1000) return lbm_fail(LBM_EINVAL, "chunks = %d outside [1, 1000]", chunks);
   if (b->t_global % kChunk != 0)
     return lbm_fail(LBM_EINVAL, "autotune only at a multiple of 100 steps");
-  std::string key = tune_key("batch", b->dtype, b->n, (long long)b->elems);
+  std::string key = tune_key("batch", kNumShapes, kShapesRevision, b->dtype, b->n,
+                             (long long)b->elems);
   int cached = use_cache ? tune_cache_lookup(key) : -1;
   if (cached >= 0 && cached < kNumShapes) {
     int rc = lbm_batch_set_option(b, LBM_OPT_STEP_VARIANT, cached);

@@ -25,8 +25,13 @@ constexpr int kChunk = 100;
 
 // Tile-shape autotuner cache: a text file named by $LBM_TUNE_CACHE with
 // lines "<key> <variant>"; the key names the device architecture, the kind
-// of handle, the storage type and the lattice size.
-std::string tune_key(const char *kind, int dtype, long long a, long long b);
+// of handle, its table of shapes, the storage type and the lattice size.  A
+// number means a shape only together with the table it was chosen from, so
+// an entry counts while the table has the same number of shapes and the same
+// revision, a constant beside the table that goes up with every change of
+// what one of its numbers runs.
+std::string tune_key(const char *kind, int shapes, int revision, int dtype, long long a,
+                     long long b);
 int tune_cache_lookup(const std::string &key);      // -1 if absent
 void tune_cache_store(const std::string &key, int variant);
 
