@@ -18,6 +18,19 @@ bool pageable(const void *p) {
   }
   return at.type == hipMemoryTypeUnregistered;
 }
+
+// Whether work issued to st runs now and is not recorded into a graph: the
+// staged copies and their events would be recorded, with the pinned buffers in
+// the caller's graph, and the wait for them would fail without ending the
+// capture.
+bool runs_now(hipStream_t st) {
+  hipStreamCaptureStatus status;
+  if (hipStreamIsCapturing(st, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return status == hipStreamCaptureStatusNone;
+}
 }  // namespace
 
 bool HostStage::ensure() {
@@ -51,7 +64,7 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
   bool staged = true;
   for (int k = 0; k < n; ++k)
     if (outs[k].dst) total += outs[k].bytes;
-  staged = total >= kMinBytes;
+  staged = total >= kMinBytes && runs_now(st);
   const bool large = total >= kLargeBytes;
   const size_t chunk = large ? kChunkBytes : kSmallChunkBytes;
   for (int k = 0; k < n && staged; ++k)
