@@ -3,7 +3,9 @@
 
 #include <algorithm>
 #include <atomic>
+#include <condition_variable>
 #include <cstring>
+#include <mutex>
 #include <thread>
 #include <vector>
 
@@ -90,7 +92,23 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
   std::atomic<bool> stop{false};
   std::atomic<int> workers{0}, left[kBufs];
   for (auto &l : left) l = 0;
+  // The first chunk comes after all that is queued on the stream, so the
+  // workers sleep until then; later chunks follow at the link's rate.
+  std::mutex mutex;
+  std::condition_variable begun;
+  bool go = false;
+  auto begin = [&]() {
+    {
+      std::lock_guard<std::mutex> lock(mutex);
+      go = true;
+    }
+    begun.notify_all();
+  };
   auto work = [&](int k) {
+    {
+      std::unique_lock<std::mutex> lock(mutex);
+      begun.wait(lock, [&] { return go; });
+    }
     for (size_t c = 0; c < chunks.size(); ++c) {
       while (ready.load(std::memory_order_acquire) <= c) {
         if (stop.load(std::memory_order_acquire)) return;
@@ -145,8 +163,10 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
     }
     if (e == hipSuccess) e = hipEventSynchronize(ev_[c % kBufs]);
     if (e == hipSuccess) ready.store(c + 1, std::memory_order_release);
+    if (c == 0 && e == hipSuccess) begin();
   }
   if (e != hipSuccess) stop.store(true, std::memory_order_release);
+  begin();
   for (std::thread &t : threads) t.join();
   return e;
 }
