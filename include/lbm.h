@@ -249,6 +249,12 @@ int lbm_steps_done(lbm_t h, int64_t *t);
 /*
  * Density and velocity (Eq. 3) at the current step, each [ny][nx] doubles.
  * A NULL output is skipped.  _host writes host memory, _dev device memory.
+ *
+ * Host results of 4 MB and more (fields, Psi, populations of any handle) into
+ * pageable memory go through pinned buffers that the process's handles share:
+ * 3 MB a call at work, 12 MB from 16 MB of results on, at most four calls at
+ * once (others copy without).  They are given back when the last handle that
+ * used them is destroyed, all but one call's.
  */
 int lbm_moments(lbm_t h, double *rho_host, double *ux_host, double *uy_host);
 int lbm_moments_device(lbm_t h, double *rho_dev, double *ux_dev,

@@ -21,10 +21,8 @@ bool pageable(const void *p) {
   return at.type == hipMemoryTypeUnregistered;
 }
 
-// Whether work issued to st runs now and is not recorded into a graph: the
-// staged copies and their events would be recorded, with the pinned buffers in
-// the caller's graph, and the wait for them would fail without ending the
-// capture.
+// Whether work issued to st runs now and is not recorded into a graph: a staged
+// copy would put the pinned buffers into the caller's graph.
 bool runs_now(hipStream_t st) {
   hipStreamCaptureStatus status;
   if (hipStreamIsCapturing(st, &status) != hipSuccess) {
@@ -33,67 +31,99 @@ bool runs_now(hipStream_t st) {
   }
   return status == hipStreamCaptureStatusNone;
 }
-}  // namespace
 
-bool HostStage::ensure() {
-  if (pin_) return true;
-  if (hipHostMalloc((void **)&pin_, kBufs * kChunkBytes, hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    pin_ = nullptr;
-    return false;
+constexpr int kBufs = 3, kMaxRings = 4;
+constexpr int kLargeHelpers = 8, kSmallHelpers = 3;
+constexpr size_t kLargeChunk = 4u << 20, kSmallChunk = 1u << 20;
+constexpr size_t kLargeBytes = 16u << 20, kMinBytes = 4u << 20;
+
+// kBufs buffers of `chunk` bytes, pinned for every device.
+struct Ring {
+  char *mem = nullptr;
+  size_t chunk = 0;
+  bool busy = false;
+};
+
+class Rings {
+ public:
+  void join() {
+    std::lock_guard<std::mutex> lock(mutex_);
+    ++users_;
   }
-  for (hipEvent_t &e : ev_)
-    if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
-      (void)hipGetLastError();
-      e = nullptr;
-      release();
-      return false;
+  void leave() {
+    std::lock_guard<std::mutex> lock(mutex_);
+    if (--users_ > 0) return;
+    Ring *keep = &ring_[0];   // the largest stays
+    for (Ring &r : ring_)
+      if (r.chunk > keep->chunk) keep = &r;
+    for (Ring &r : ring_)
+      if (&r != keep && !r.busy) drop(r);
+  }
+  // An idle ring of at least `chunk` bytes a buffer, marked busy; null if all
+  // are in use or there is no memory.
+  Ring *take(size_t chunk) {
+    std::lock_guard<std::mutex> lock(mutex_);
+    Ring *best = nullptr;   // the smallest that serves, else an empty place, else any
+    auto rank = [&](const Ring &r) { return r.chunk >= chunk ? 0 : r.mem ? 2 : 1; };
+    for (Ring &r : ring_)
+      if (!r.busy && (!best || rank(r) < rank(*best) ||
+                      (rank(r) == 0 && rank(*best) == 0 && r.chunk < best->chunk)))
+        best = &r;
+    if (!best) return nullptr;
+    if (best->chunk < chunk) {
+      drop(*best);
+      if (hipHostMalloc((void **)&best->mem, kBufs * chunk, hipHostMallocPortable) !=
+          hipSuccess) {
+        (void)hipGetLastError();
+        best->mem = nullptr;
+        return nullptr;
+      }
+      best->chunk = chunk;
     }
-  return true;
-}
-
-void HostStage::release() {
-  for (hipEvent_t &e : ev_) {
-    if (e) (void)hipEventDestroy(e);
-    e = nullptr;
+    best->busy = true;
+    return best;
   }
-  if (pin_) (void)hipHostFree(pin_);
-  pin_ = nullptr;
-}
+  void give(Ring *r) {
+    std::lock_guard<std::mutex> lock(mutex_);
+    r->busy = false;
+  }
 
-hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
-  size_t total = 0;
-  bool staged = true;
+ private:
+  static void drop(Ring &r) {
+    if (r.mem) (void)hipHostFree(r.mem);
+    r = Ring{};
+  }
+  std::mutex mutex_;
+  Ring ring_[kMaxRings];
+  int users_ = 0;
+};
+Rings g_rings;
+
+hipError_t copy_plain(const CopyOut *outs, int n, hipStream_t st) {
   for (int k = 0; k < n; ++k)
-    if (outs[k].dst) total += outs[k].bytes;
-  staged = total >= kMinBytes && runs_now(st);
-  const bool large = total >= kLargeBytes;
-  const size_t chunk = large ? kChunkBytes : kSmallChunkBytes;
-  for (int k = 0; k < n && staged; ++k)
-    if (outs[k].dst) staged = pageable(outs[k].dst);
-  std::vector<CopyOut> chunks;
-  std::vector<std::thread> threads;
-  if (staged) {
-    try {
-      for (int k = 0; k < n; ++k)
-        for (size_t o = 0; outs[k].dst && o < outs[k].bytes; o += chunk)
-          chunks.push_back({(char *)outs[k].dst + o, (const char *)outs[k].src + o,
-                            std::min(chunk, outs[k].bytes - o)});
-      threads.reserve(kThreads);
-      staged = ensure();
-    } catch (...) {
-      staged = false;
+    if (outs[k].dst) {
+      const hipError_t e =
+          hipMemcpyAsync(outs[k].dst, outs[k].src, outs[k].bytes, hipMemcpyDeviceToHost, st);
+      if (e != hipSuccess) return e;
     }
-  }
+  return hipStreamSynchronize(st);
+}
 
+// Copy the chunks into the buffers at pin (`chunk` bytes each) in turn; up to
+// `most` helpers move each one on, a slice each, while the next one comes.
+// Started threads go into `helpers`; with none, e is hipErrorNotReady and
+// nothing has been issued.
+hipError_t copy_staged(const std::vector<CopyOut> &chunks, char *pin, size_t chunk,
+                       std::vector<std::thread> &helpers, int most, hipStream_t st) {
   // ready: chunks that have arrived in their buffer; left[b]: slices of buffer
-  // b that are still to be moved on
+  // b that are still to be moved on; parts: slices of a chunk (set before go)
   std::atomic<size_t> ready{0};
   std::atomic<bool> stop{false};
-  std::atomic<int> workers{0}, left[kBufs];
+  std::atomic<int> left[kBufs];
   for (auto &l : left) l = 0;
+  int parts = 0;
   // The first chunk comes after all that is queued on the stream, so the
-  // workers sleep until then; later chunks follow at the link's rate.
+  // helpers sleep until then; later chunks follow at the link's rate.
   std::mutex mutex;
   std::condition_variable begun;
   bool go = false;
@@ -104,7 +134,7 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
     }
     begun.notify_all();
   };
-  auto work = [&](int k) {
+  auto help = [&](int k) {
     {
       std::unique_lock<std::mutex> lock(mutex);
       begun.wait(lock, [&] { return go; });
@@ -114,61 +144,79 @@ hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
         if (stop.load(std::memory_order_acquire)) return;
         std::this_thread::yield();
       }
-      const int T = workers.load(std::memory_order_relaxed), b = (int)(c % kBufs);
+      const int b = (int)(c % kBufs);
       auto cut = [&](int j) {   // slices of whole pages
-        return j == T ? chunks[c].bytes : chunks[c].bytes * j / T / 4096 * 4096;
+        return j == parts ? chunks[c].bytes : chunks[c].bytes * j / parts / 4096 * 4096;
       };
-      std::memcpy((char *)chunks[c].dst + cut(k), pin_ + b * kChunkBytes + cut(k),
+      std::memcpy((char *)chunks[c].dst + cut(k), pin + b * chunk + cut(k),
                   cut(k + 1) - cut(k));
       left[b].fetch_sub(1, std::memory_order_release);
     }
   };
-  if (staged) {
-    const unsigned hw = std::thread::hardware_concurrency();
-    const int most = large ? kThreads : kThreads / 2;
-    const int want = hw ? std::min<int>(most, (int)hw) : most;
-    try {
-      for (int k = 0; k < want; ++k) threads.emplace_back(work, k);
-    } catch (...) {   // as many as there are
-    }
-    staged = !threads.empty();
+  const unsigned hw = std::thread::hardware_concurrency();
+  if (hw) most = std::min(most, (int)hw);
+  try {
+    for (int k = 0; k < most; ++k) helpers.emplace_back(help, k);
+  } catch (...) {   // as many as there are
   }
-  if (!staged) {
-    for (int k = 0; k < n; ++k)
-      if (outs[k].dst) {
-        hipError_t e =
-            hipMemcpyAsync(outs[k].dst, outs[k].src, outs[k].bytes, hipMemcpyDeviceToHost, st);
-        if (e != hipSuccess) return e;
-      }
-    return hipStreamSynchronize(st);
-  }
-
-  const int T = (int)threads.size();
-  workers.store(T, std::memory_order_relaxed);   // published by the first `ready`
+  parts = (int)helpers.size();
+  if (parts == 0) return hipErrorNotReady;
   hipError_t e = hipSuccess;
-  size_t issued = 0;
   for (size_t c = 0; c < chunks.size() && e == hipSuccess; ++c) {
-    while (issued < chunks.size() && issued < c + kBufs && e == hipSuccess) {
-      const int b = (int)(issued % kBufs);
-      if (left[b].load(std::memory_order_acquire)) {
-        if (issued > c) break;   // buffer busy, chunk c is on its way
-        std::this_thread::yield();
-        continue;
-      }
-      left[b].store(T, std::memory_order_relaxed);
-      e = hipMemcpyAsync(pin_ + b * kChunkBytes, chunks[issued].src, chunks[issued].bytes,
-                         hipMemcpyDeviceToHost, st);
-      if (e == hipSuccess) e = hipEventRecord(ev_[b], st);
-      ++issued;
-    }
-    if (e == hipSuccess) e = hipEventSynchronize(ev_[c % kBufs]);
-    if (e == hipSuccess) ready.store(c + 1, std::memory_order_release);
-    if (c == 0 && e == hipSuccess) begin();
+    const int b = (int)(c % kBufs);
+    while (left[b].load(std::memory_order_acquire)) std::this_thread::yield();
+    e = hipMemcpyAsync(pin + b * chunk, chunks[c].src, chunks[c].bytes, hipMemcpyDeviceToHost,
+                       st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) break;
+    left[b].store(parts, std::memory_order_relaxed);
+    ready.store(c + 1, std::memory_order_release);
+    if (c == 0) begin();
   }
   if (e != hipSuccess) stop.store(true, std::memory_order_release);
   begin();
-  for (std::thread &t : threads) t.join();
+  for (std::thread &t : helpers) t.join();
   return e;
+}
+}  // namespace
+
+void HostStage::release() {
+  if (user_) g_rings.leave();
+  user_ = false;
+}
+
+hipError_t HostStage::copy(const CopyOut *outs, int n, hipStream_t st) {
+  size_t total = 0;
+  for (int k = 0; k < n; ++k)
+    if (outs[k].dst) total += outs[k].bytes;
+  bool staged = total >= kMinBytes && runs_now(st);
+  for (int k = 0; k < n && staged; ++k)
+    if (outs[k].dst) staged = pageable(outs[k].dst);
+  if (!staged) return copy_plain(outs, n, st);
+
+  const bool large = total >= kLargeBytes;
+  const size_t chunk = large ? kLargeChunk : kSmallChunk;
+  const int most = large ? kLargeHelpers : kSmallHelpers;
+  std::vector<CopyOut> chunks;
+  std::vector<std::thread> helpers;
+  Ring *ring = nullptr;
+  try {
+    for (int k = 0; k < n; ++k)
+      for (size_t o = 0; outs[k].dst && o < outs[k].bytes; o += chunk)
+        chunks.push_back({(char *)outs[k].dst + o, (const char *)outs[k].src + o,
+                          std::min(chunk, outs[k].bytes - o)});
+    helpers.reserve(most);
+    if (!user_) g_rings.join();
+    user_ = true;
+    ring = g_rings.take(chunk);
+  } catch (...) {   // no host memory
+  }
+  if (!ring) return copy_plain(outs, n, st);
+  const hipError_t e = copy_staged(chunks, ring->mem, chunk, helpers, most, st);
+  // after an error the copy into the ring may still be running
+  if (e == hipSuccess || e == hipErrorNotReady || hipStreamSynchronize(st) == hipSuccess)
+    g_rings.give(ring);
+  return e == hipErrorNotReady ? copy_plain(outs, n, st) : e;
 }
 
 }  // namespace lbm
