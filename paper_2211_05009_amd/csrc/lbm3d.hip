@@ -26,33 +26,57 @@ namespace {
 constexpr int kNum3Variants = 8;
 // The shape a new handle starts with (lbm3d_autotune refines it).  The
 // two-step shapes read and write the state once for two steps; what they cost
-// on a small box is the last, partly filled round of blocks (one block per CU).
+// is the halo, sites of their tiles that lie outside the box, and the last,
+// partly filled round of blocks (one block per CU).  The one-step shape pays
+// for whole rows of 64 (n64 sites in all).
 // Measured on one MI355X, us per step, one-step shape 1 / shape 3 / shape 4:
-//   FP32: 48 x 40 x 64  6.6 / 4.4 / 6.2     96^3          23.1 / 18.9 / 21.9
-//         64^3          8.4 / 5.8 / 7.1     128^3         63.6 / 49.8 / 41.1
-//         40 x 150 x 60 13.6 / 13.3 / 13.4  256^3         516 / 407 / 293
-//   FP64: 32^3          5.7 / 3.9 / 5.9     64 x 64 x 192 36.2 / 35.0 / 34.7
-//         48 x 40 x 64  8.7 / 7.4 / 8.1     96^3          58.5 / 41.3 / 36.2
-//         180 x 33 x 33 10.8 / 12.2 / 11.7  192^3         418 / 344 / 245
-// So: columns marching through z (4) on a box that streams from the memory
-// behind the caches, from 1.2 M sites in FP32 and 0.7 M in FP64; below that
-// the 3-D tile (3), in FP64 only while its tiles take at most two rounds of
-// the 256 CUs (its 16 x 6 x 4 tiles recompute 2.25 of every site, and the
-// one-step shape ties or wins from the third round on).  A box so thin that
-// its sites fill less than 40 % of the tiles stays with the one-step shape.
+//   FP32: 48 x 40 x 64  6.7 / 4.4 / 6.2     96^3          23.1 / 18.9 / 21.9
+//         64^3          8.2 / 5.9 / 7.5     128^3         60.4 / 49.7 / 41.2
+//         40 x 150 x 60 13.7 / 13.5 / 13.7  256^3         506 / 399 / 285
+//   FP64: 32^3          5.8 / 3.6 / 5.6     85^3          43.4 / 36.5 / 32.0
+//         48 x 40 x 64  8.7 / 7.4 / 8.1     96^3          57.0 / 41.3 / 36.3
+//         64^3          12.8 / 12.1 / 15.0  192^3         415 / 342 / 241
+//         80^3          25.3 / 24.6 / 23.6
+// The state of a large box streams from the memory behind the caches and the
+// columns marching through z (4) win by up to 2.4 times.  Just above the line (1.2
+// M sites in FP32, 0.7 M in FP64; both buffers still fit 256 MB) they also
+// have to fill 60 % of their columns and, in FP32, 16 planes: 350 x 9 x 391 30.8
+// against 37.0 us, 374 x 242 x 14 27.4 / 30.9; FP64 757 x 13 x 101 56.6 / 58.7.
+// Above that 40 % (n64 1.75 M and 1.05 M; 31 x 92 x 789 FP32: 1.7 times faster
+// at 46 %; 199 x 17 x 385, 1.68 M at 55 %: 35.3 against 41.3 us).
+// Below the line the 3-D tile (3) wins whenever its tiles take one round of
+// the 256 CUs and are 40 % full.  With more rounds it wins where the one-step
+// rows are badly filled, too, or the box is a cube: FP32 at 66^3 9.3 against
+// 12.8 us (n64 1.19 times the tiles' sites), 100^3 27.9 / 29.1 (0.96), but
+// 200 x 200 x 10 13.6 / 12.6, 228 x 12 x 242 20.7 / 18.0 (0.74), 300 x 50 x 50
+// 19.9 / 19.4 (0.86) and 160 x 771 x 9 31.9 / 23.8 (0.90).  FP64 tiles recompute
+// 2.25 of every site: two rounds at 0.9 (48^3 7.4 / 8.7 at 1.33, 391 x 13 x 16 8.4
+// / 7.1 at 0.81), and from the third round on the one-step shape, which by box
+// is up to 15 % slower or 40 % faster there (64^3 12.1 / 12.8, 56^3 11.3 / 10.0,
+// 780 x 75 x 9 35.4 / 25.2).  From 0.6 M sites shape 4 would win on boxes like
+// 85^3, too; lbm3d_autotune finds it.
+// On 324 random boxes of 20 k to 6 M sites and both types this start takes 0.78
+// of the one-step shape's time (geometric mean); it is more than 4 % slower on
+// two (121 x 265 x 35 FP32 6 %, 178 x 12 x 56 FP64 10 %).
 int default_shape3(int nx, int ny, int nz, int dtype) {
   const bool f64 = dtype == LBM_F64;
-  const long long n = (long long)nx * ny * nz;
+  const long long n = (long long)nx * ny * nz, n64 = (nx + 63) / 64 * 64LL * ny * nz;
   auto tiles = [&](int tx, int ty, int tz) {
     return (long long)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty) * ((nz + tz - 1) / tz);
   };
   if (n >= (f64 ? 700000 : 1200000)) {
     const int tx = f64 ? 32 : 64, ty = f64 ? 12 : 8;
-    return 5 * n >= 2 * tiles(tx, ty, 1) * tx * ty ? 4 : 1;
+    const long long in_columns = tiles(tx, ty, 1) * tx * ty;
+    if (n64 >= (f64 ? 1050000 : 1750000)) return 5 * n >= 2 * in_columns ? 4 : 1;
+    return 5 * n >= 3 * in_columns && (f64 || nz >= 16) ? 4 : 1;
   }
   const int tx = f64 ? 16 : 32, ty = f64 ? 6 : 8, tz = 4;
-  const long long nt = tiles(tx, ty, tz);
-  return 5 * n >= 2 * nt * tx * ty * tz && (!f64 || nt <= 512) ? 3 : 1;
+  const long long nt = tiles(tx, ty, tz), in_tiles = nt * tx * ty * tz;
+  if (5 * n < 2 * in_tiles) return 1;
+  if (nt <= 256) return 3;
+  if (f64) return nt <= 512 && 10 * n64 >= 9 * in_tiles ? 3 : 1;
+  if (nt <= 512) return 20 * n64 >= 17 * in_tiles ? 3 : 1;
+  return nz >= 16 && 25 * n64 >= 23 * in_tiles ? 3 : 1;
 }
 
 // blocks of the monitor and mass reductions (each thread takes a few sites:
