@@ -163,12 +163,42 @@ void conv_fd(const ConvArgs &a, hipStream_t st) {
   // are taken where they give more than one block per CU; with fewer, 4 x 32
   // (4 rows per wave, twice the blocks) hide more: 64 > 128 channels at
   // 32 x 64, batch 8: 6.25 against 6.7 us, its input gradient 6.4 against
-  // 8.5 us; at 512 blocks (64 > 64 at 64 x 128) 13.4 against 11.7 us.
+  // 8.5 us; at 512 blocks (64 > 64 at 64 x 128) 13.4 against 11.7 us.  Images
+  // of up to 4 rows would leave half of an 8-row tile empty: 128 > 384 at 2 x 128,
+  // batch 16, 10.0 against 13.1 us.
+  //
+  // An input gradient without packed weights reads them from the rows, 64 of
+  // 128 bytes of a line at a time, which two blocks of a CU do not keep up: with
+  // several chunks a taller tile is taken as soon as the lower one would give
+  // more than one block per CU, of 8 or 10 rows by the rows that the fullest CU
+  // gets.  64 > 256 at 128 x 64, batch 4: 21.0 us by 4 x 32 tiles (512 blocks),
+  // 13.7 by 8 x 32; 384 > 128 at 18 x 64, batch 8: 19.9 us by 8 x 32 (576), 15.0
+  // by 10 x 32 (384); at 20 x 16 12.1 by 8 x 16 (288), 8.7 by 16 x 16.  (Whole-row
+  // tiles with the weights in LDS took 18.3, 15.2 and 9.1 us; on images of 2 or 4
+  // rows with hundreds of blocks they were faster, 384 > 128 at 2 x 128, batch
+  // 16, 11.3 against 16.5 us.)
   if (tile_path(a.w, a.h, a.os, a.oo) && (MODE != FWD || a.wf) &&
       (long long)a.h * a.w * a.xs * 2 < 0x7f000000LL) {
+    auto blocks = [&](int th, int tw) {   // of th x tw pixels
+      return (long long)a.n * ((a.h + th - 1) / th) * (a.w / tw) * (N / 32);
+    };
+    if constexpr (MODE == DGRAD) {
+      auto rows = [&](int th, int tw, int r) { return r * ((blocks(th, tw) + 255) / 256); };
+      if (!a.wf && a.co > 32) {
+        if (a.w == 16 && a.h > 8 && blocks(8, 16) > 256) {
+          if (rows(20, 16, 10) < rows(16, 16, 8)) return conv_tile<MODE, 10, 2, 1>(a, st);
+          return conv_tile<MODE, 8, 2, 1>(a, st);
+        }
+        if (a.w > 16 && a.h > 4 && blocks(4, 32) > 256) {
+          if (rows(10, 32, 10) < rows(8, 32, 8)) return conv_tile<MODE, 10, 1, 2>(a, st);
+          return conv_tile<MODE, 8, 1, 2>(a, st);
+        }
+        return a.w == 16 ? conv_tile<MODE, 4, 2, 1>(a, st) : conv_tile<MODE, 4, 1, 2>(a, st);
+      }
+    }
     if (a.w == 16)
       conv_tile<MODE, 4, 2, 1>(a, st);
-    else if ((long long)a.n * ((a.h + 7) / 8) * (a.w / 32) * (N / 32) > 256)
+    else if (a.h > 4 && blocks(8, 32) > 256)
       conv_tile<MODE, 8, 1, 2>(a, st);
     else
       conv_tile<MODE, 4, 1, 2>(a, st);
