@@ -73,7 +73,7 @@ __device__ __forceinline__ void block_best(double (&v)[kVortexRegions], int (&k)
 //   midpoint rule on site centres;
 //   on-node walls (g.on_node): Psi(0) = 0, Psi(y) = Psi(y - 1) - (u_x(y - 1)
 //   + u_x(y)) / 2, the trapezoid rule.
-// A block owns kPsiCols columns and takes them kPsiRows rows at a time: all
+// A block owns kPsiCols columns and takes them 64 J rows at a time: all
 // its threads compute the terms of the sum (u_x; on nodes the half sum of
 // neighbours, exact scalings of what the formula adds) into LDS, one lane
 // per column replaces them by the running sums in row order (an addition
@@ -83,17 +83,19 @@ __device__ __forceinline__ void block_best(double (&v)[kVortexRegions], int (&k)
 // [region][block].  *zero (if not null) is cleared for the kernel after it.
 // Bound by latency: the loads of a tile, then its chain of additions (about
 // 12 cycles a row).  500 x 600 FP64: 20 us, 28 with the extrema; one thread
-// per column, nine loads and the addition row by row, took 290 us.
-constexpr int kPsiThreads = 512, kPsiCols = 8, kPsiRows = 512;
-template <typename T, bool SHIFT, bool EXT, bool NODE>
+// per column, nine loads and the addition row by row, took 290 us.  J = 8 rows
+// per thread; 1 on lattices of up to 64 rows, where the other seven would
+// be beyond the lattice (16 x 16 FP64, whole call: 27.0 -> 24.0 us).
+constexpr int kPsiThreads = 512, kPsiCols = 8;
+template <typename T, bool SHIFT, bool EXT, bool NODE, int J>
 __global__ __launch_bounds__(kPsiThreads) void k_psi(const T *__restrict__ s, Geometry g,
                                                      double *__restrict__ psi,
                                                      double *__restrict__ pv,
                                                      int *__restrict__ pk,
                                                      unsigned int *__restrict__ zero) {
-  constexpr int C = kPsiCols, J = kPsiRows * C / kPsiThreads;   // rows per thread and tile
-  constexpr int E = NODE ? 1 : 0;                               // and the row below them
-  __shared__ double col[kPsiRows * C];
+  constexpr int C = kPsiCols, R = J * kPsiThreads / C;   // rows of a tile, J per thread
+  constexpr int E = NODE ? 1 : 0;                        // and the row below them
+  __shared__ double col[R * C];
   const int c = threadIdx.x % C, r0 = threadIdx.x / C * J;
   const int b = xcd_tile(blockIdx.x, gridDim.x);
   const int x = b * C + c, nx = g.nx, ny = g.ny, hy = min(ny, nx / 2);
@@ -125,8 +127,8 @@ __global__ __launch_bounds__(kPsiThreads) void k_psi(const T *__restrict__ s, Ge
     }
   };
   load(0);
-  for (int yb = 0; yb < ny; yb += kPsiRows) {
-    const int rows = min(kPsiRows, ny - yb);
+  for (int yb = 0; yb < ny; yb += R) {
+    const int rows = min(R, ny - yb);
     double half[J];                 // half-way walls: u_x / 2 of the site itself
 #pragma unroll
     for (int j = 0; j < J; ++j) {
@@ -136,15 +138,15 @@ __global__ __launch_bounds__(kPsiThreads) void k_psi(const T *__restrict__ s, Ge
       col[(r0 + j) * C + c] = t;
     }
     __syncthreads();
-    if (yb + kPsiRows < ny) load(yb + kPsiRows);
+    if (yb + R < ny) load(yb + R);
     if (threadIdx.x < C) {   // the next U terms are read while U are summed
       constexpr int U = 16;
-      static_assert(kPsiRows % U == 0, "whole groups");
+      static_assert(R % U == 0, "whole groups");
       double u[U], nu[U];
 #pragma unroll
       for (int j = 0; j < U; ++j) u[j] = col[j * C + c];
       for (int r = 0; r < rows; r += U) {
-        double *at = col + r * C + c, *next = r + U < kPsiRows ? at + U * C : at;
+        double *at = col + r * C + c, *next = r + U < R ? at + U * C : at;
 #pragma unroll
         for (int j = 0; j < U; ++j) nu[j] = next[j * C];
 #pragma unroll
@@ -193,7 +195,7 @@ __global__ __launch_bounds__(kPsiThreads) void k_psi(const T *__restrict__ s, Ge
 
 // What the host reads of a vortex call, copied in one piece: the extrema,
 // the number of centres, and the first kVortexFirst of them (the rest
-// follow at cap-dependent places; see find_centres in lbm.hip).
+// are fetched by a second copy; see find_vortices in lbm.hip).
 constexpr int kVortexFirst = 64;
 struct VortexOut {
   double v[kVortexRegions];

@@ -21,6 +21,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/lbm.h"
@@ -706,19 +707,22 @@ template <typename T, bool S>
 static void launch_psi_t(lbm_cavity *h, double *psi, double *pv, int *pk, unsigned int *zero) {
   const dim3 grid(psi_blocks(h)), block(kPsiThreads);
   const T *src = (const T *)h->buf[h->cur];
+  auto go = [&](auto ext, auto node) {
+    constexpr bool E = decltype(ext)::value, N = decltype(node)::value;
+    if (h->ny <= 64)
+      hipLaunchKernelGGL((k_psi<T, S, E, N, 1>), grid, block, 0, h->stream, src, geom(h), psi,
+                         pv, pk, zero);
+    else
+      hipLaunchKernelGGL((k_psi<T, S, E, N, 8>), grid, block, 0, h->stream, src, geom(h), psi,
+                         pv, pk, zero);
+  };
+  using yes = std::true_type;
+  using no = std::false_type;
   const bool node = h->wall == LBM_WALL_NEE;
-  if (pv && node)
-    hipLaunchKernelGGL((k_psi<T, S, true, true>), grid, block, 0, h->stream, src, geom(h), psi,
-                       pv, pk, zero);
-  else if (pv)
-    hipLaunchKernelGGL((k_psi<T, S, true, false>), grid, block, 0, h->stream, src, geom(h), psi,
-                       pv, pk, zero);
-  else if (node)
-    hipLaunchKernelGGL((k_psi<T, S, false, true>), grid, block, 0, h->stream, src, geom(h), psi,
-                       pv, pk, zero);
-  else
-    hipLaunchKernelGGL((k_psi<T, S, false, false>), grid, block, 0, h->stream, src, geom(h), psi,
-                       pv, pk, zero);
+  if (pv && node) go(yes{}, yes{});
+  else if (pv) go(yes{}, no{});
+  else if (node) go(no{}, yes{});
+  else go(no{}, no{});
 }
 
 // ------------------------------------------------------------------- C ABI
