@@ -638,7 +638,10 @@ int lbm_batch_autotune(lbm_batch_t b, int chunks, int use_cache,
 typedef struct lbm_surrogate *lbm_sur_t;
 
 /* A surrogate for batches of up to max_batch (1..256) samples; parameters
- * start at zero (load them with lbm_sur_set_params). */
+ * start at zero (load them with lbm_sur_set_params).  The handle holds the
+ * device memory of forecasts and of training until it is destroyed; 64 MB of
+ * it, whatever max_batch, let a training step add the weight gradients' partial
+ * sums of several layers in one launch. */
 int lbm_sur_create(int max_batch, lbm_sur_t *out);
 int lbm_sur_destroy(lbm_sur_t s);
 /* Work is issued on hip_stream (NULL: a stream of the handle's own).  The

@@ -5,9 +5,10 @@
 // advances all active cavities by one step (k_step_batch over a tile table);
 // a chunk of `graph_steps` steps (default 1000, a multiple of the 100-step
 // monitor cadence) with the per-cavity FP64 monitors after every 100 steps is
-// captured once into a HIP graph and replayed.  Cavities whose Eq. 6
-// residual falls below a threshold drop out of the tile table at a chunk
-// boundary.  Chunk boundaries are reached at even step counts only, so the
+// captured once into a HIP graph and replayed; a call that does not fill it
+// replays a second graph of one 100-step chunk, and takes single steps off
+// that grid.  Cavities whose Eq. 6 residual falls below a threshold drop out of
+// the tile table at a chunk boundary.  Chunk boundaries are reached at even step counts only, so the
 // current buffer of every cavity, active or not, is buf[0] there.
 #include <hip/hip_runtime.h>
 
