@@ -131,8 +131,8 @@ void conv_mn(const ConvArgs &a, int M, int N, hipStream_t st) {
   hipLaunchKernelGGL((k_conv_mn<MODE, WM, WN, TM, TN>), grid, dim3(256), 0, st, a);
 }
 
-// One forward or input-gradient pass by k_conv_tile.
-template <int MODE, int RT, int WR, int WC>
+// One forward or input-gradient pass by k_conv_tile (ONE: also of one chunk).
+template <int MODE, int RT, int WR, int WC, bool ONE = true>
 void conv_tile(const ConvArgs &a, hipStream_t st) {
   const int ntx = a.w / (16 * WC), nty = (a.h + RT * WR - 1) / (RT * WR);
   const dim3 grid(a.n * ntx * nty * ((MODE == FWD ? a.co : a.ci) / 32));
@@ -142,10 +142,13 @@ void conv_tile(const ConvArgs &a, hipStream_t st) {
   };
   using yes = std::true_type;
   using no = std::false_type;
-  if ((MODE == FWD ? a.ci : a.co) > 32) return go(no{}, no{});
-  if constexpr (MODE == FWD && WC == 2)
-    if (a.enc || a.head) return go(yes{}, yes{});
-  go(yes{}, no{});
+  if constexpr (ONE)
+    if ((MODE == FWD ? a.ci : a.co) == 32) {
+      if constexpr (MODE == FWD && WC == 2)
+        if (a.enc || a.head) return go(yes{}, yes{});
+      return go(yes{}, no{});
+    }
+  go(no{}, no{});
 }
 
 // Whether conv_fd takes k_conv_tile for a w x h image: widths of whole tiles,
@@ -186,11 +189,11 @@ void conv_fd(const ConvArgs &a, hipStream_t st) {
       auto rows = [&](int th, int tw, int r) { return r * ((blocks(th, tw) + 255) / 256); };
       if (!a.wf && a.co > 32) {
         if (a.w == 16 && a.h > 8 && blocks(8, 16) > 256) {
-          if (rows(20, 16, 10) < rows(16, 16, 8)) return conv_tile<MODE, 10, 2, 1>(a, st);
-          return conv_tile<MODE, 8, 2, 1>(a, st);
+          if (rows(20, 16, 10) < rows(16, 16, 8)) return conv_tile<MODE, 10, 2, 1, false>(a, st);
+          return conv_tile<MODE, 8, 2, 1, false>(a, st);
         }
         if (a.w > 16 && a.h > 4 && blocks(4, 32) > 256) {
-          if (rows(10, 32, 10) < rows(8, 32, 8)) return conv_tile<MODE, 10, 1, 2>(a, st);
+          if (rows(10, 32, 10) < rows(8, 32, 8)) return conv_tile<MODE, 10, 1, 2, false>(a, st);
           return conv_tile<MODE, 8, 1, 2>(a, st);
         }
         return a.w == 16 ? conv_tile<MODE, 4, 2, 1>(a, st) : conv_tile<MODE, 4, 1, 2>(a, st);
